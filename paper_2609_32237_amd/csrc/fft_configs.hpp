@@ -153,13 +153,14 @@ struct Configs<4096> {
     // comparisons on two boxes (181.2 -> 179.0 us on one), and moved the SAR
     // chain by -0.4 to +1.4 us; with an FP32 intermediate they cost the SAR
     // chain 1.6-2.7 us, so those rows keep the computed factors
-    // matched columns (the SAR azimuth pass) reading an FP32 intermediate:
-    // the 4-column strips, two workgroups per CU, took the chain from
-    // 140.9 to 134.8-134.9 us (same process, two runs); with an FP16
-    // intermediate (16-byte pieces) they measured 125.5-126.3 against
-    // 125.2-126.0 us, so those keep the 8-column strips
+    // matched columns (the SAR azimuth pass): bound by the 64-byte pieces of
+    // the image rows (128 MiB strided reads alone take 34 us, writes 24 us);
+    // the 4-column strips' 32-byte pieces cost more.  Image after image, on
+    // inputs that no cache holds, an FP32 chain takes 145 us with 8 columns
+    // and 157 with 4 (FP16 124 and 128); a single chain after a flush, where
+    // the intermediate is still in the Infinity Cache, 141 and 135.
     static constexpr int kRowDefault[2] = {8, 1}, kColDefault[2] = {5, 5};
-    static constexpr int kRowMatched[2] = {1, 9}, kColMatched[2] = {6, 5};
+    static constexpr int kRowMatched[2] = {1, 9}, kColMatched[2] = {5, 5};
 };
 template <>
 struct Configs<8192> {
@@ -232,6 +233,24 @@ template <>
 struct SmallRows<2048> {
     static constexpr int variant = 4;
     static constexpr long long below = 2 * 256;
+};
+
+// Few columns: the 8-column strips of 4096 points fill a CU each, so 1024
+// columns or fewer leave half of the 256 CUs idle; 4-column strips of 16
+// points per thread (1024 threads) use twice as many CUs with twice the waves.
+// Measured, plain transform: 250 columns 14.8 against 19.0 us (FP32) and 12.4
+// against 15.8 (FP16), 512 columns 16.4 / 21.3, 1000 columns 18.1 / 19.2, but
+// 1536 columns 46.9 / 32.0; SAR chain of 4096 x 1024 52.5 / 56.9 (FP16
+// intermediate 44.6 / 51.6).
+template <int N>
+struct SmallCols {
+    static constexpr int variant = -1;      // index into Cols, or none
+    static constexpr long long most = 0;    // applies to this many columns or fewer
+};
+template <>
+struct SmallCols<4096> {
+    static constexpr int variant = 2;
+    static constexpr long long most = 4 * 256;
 };
 
 template <int I, class L>
@@ -440,6 +459,7 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
             v = ScaleCols<N>::v[half];
         } else {
             v = mf ? Configs<N>::kColMatched[half] : Configs<N>::kColDefault[half];
+            if (a.batch <= SmallCols<N>::most) v = SmallCols<N>::variant;
         }
     }
     return with_variant(v, Cols{}, f);
