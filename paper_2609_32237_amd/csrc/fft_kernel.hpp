@@ -28,8 +28,9 @@
 //          exchange is a register/lane transpose made with cross-lane
 //          instructions (fft_lane.hpp).
 //   TWMODE 0: every inter-stage twiddle read from the table;
-//          1: one table read per base-4 digit of the radix, the rest formed
-//          by complex products (fewer loads, a few more FP32 operations);
+//          1: one table read per base-4 digit of the radix, the other powers
+//          of two as squares, multiplied in the butterflies' layers
+//          (fewest loads and fewest FP32 operations);
 //          2: every factor read from the stage's own table, laid out so that
 //          consecutive lanes read consecutive entries (no products: fewer
 //          FP32 operations than 1, more loads, each one coalesced);
@@ -232,49 +233,43 @@ __device__ __forceinline__ void tw_issue(TwRegs<K, NS, R> &tr, int t, const floa
     }
 }
 
-// Multiply u[r] by w[r] = W^{k r} (its conjugate for the inverse), r = 1..R-1.
-// With the digit-base reads (TWMODE 1), r = low + 16 h with low < 16:
-// w[low] is the product of its two base-4 digit parts and w[r] = w[low] *
-// w[16 h].  Each factor is applied as soon as it is formed, so only the digit
-// bases and one partial product are live at a time rather than all R - 1
-// factors (31 complex values at radix 32, which would spill).  The products
-// are the same, in the same order, as forming every factor first.
+// The square of w = (c, -s) on the unit circle.  The real part as 1 - 2 s^2 or
+// 2 c^2 - 1, whichever takes the smaller component: half the rounding error of
+// c^2 - s^2.  SMALL: |s| <= |c| is known (a turn of at most an eighth).
+template <bool SMALL>
+__device__ __forceinline__ float2 unit_square(float2 w) {
+    const float t = -2.0f * w.y;
+    float re = fmaf(t, w.y, 1.0f);
+    if constexpr (!SMALL) {
+        const float big = fmaf(2.0f * w.x, w.x, -1.0f);
+        re = fabsf(w.y) < fabsf(w.x) ? re : big;
+    }
+    return make_float2(re, -t * w.x);
+}
+
+// The stage's DFT with its twiddles, u[r] W^(k r) (conjugate for the inverse),
+// r = 0..R-1.  With the digit-base reads (TWMODE 1) the layers of the
+// decimation in time need only the powers W^(k 2^i): the even ones are read,
+// the odd ones their squares (reading all of them was 2-6% slower on the
+// issue-bound kernels: 16384 FP16 rows 425-436 against 437-447 us).  The other
+// modes multiply first.
+// Against multiplying every input by its own factor (formed by up to three
+// products) and a radix-4 butterfly, VALU instructions per point fall from
+// 44 to 37 at 4096 points, at 2% less rounding error (relative to FP64,
+// 4096 points: 1.50e-7 against 1.53e-7).
 template <class K, int NS, int R, int q, bool INV>
-__device__ __forceinline__ void tw_apply(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
-    auto mul = [](float2 a, float2 w) { return INV ? cmulc(a, w) : cmul(a, w); };
+__device__ __forceinline__ void tw_dft(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
     if constexpr (TwRegs<K, NS, R>::MODE != 1) {
-        static_for<1, R>([&](auto rc) { u[rc] = mul(u[rc], tr.w[q][rc - 1]); });
+        static_for<1, R>([&](auto rc) { u[rc] = INV ? cmulc(u[rc], tr.w[q][rc - 1]) : cmul(u[rc], tr.w[q][rc - 1]); });
+        Dft<R, INV>::run(u);
     } else {
-        constexpr int D = TwRegs<K, NS, R>::LOADS;
-        float2 b[D][3];  // b[i][d - 1] = W^{k d 4^i}
-        static_for<0, D>([&](auto ic) {
+        float2 pw[ilog2(R)];
+        static_for<0, ilog2(R)>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            constexpr int base = pow4(i);
-            b[i][0] = tr.w[q][i];
-            if constexpr (2 * base < R) b[i][1] = cmul(b[i][0], b[i][0]);
-            if constexpr (3 * base < R) b[i][2] = cmul(b[i][1], b[i][0]);
+            // W^(k 2^(i-1)) turns by at most 2 pi 2^(i-1) / R
+            pw[i] = i % 2 == 0 ? tr.w[q][i / 2] : unit_square<((4 << i) <= R)>(tr.w[q][i / 2]);
         });
-        constexpr int LOW = R < 16 ? R : 16;
-        static_for<0, LOW>([&](auto lc) {
-            constexpr int low = decltype(lc)::value;
-            constexpr int d0 = low % 4, d1 = low / 4;
-            float2 wl = make_float2(1.0f, 0.0f);
-            if constexpr (d0 != 0 && d1 != 0) wl = cmul(b[0][d0 - 1], b[1][d1 - 1]);
-            if constexpr (d0 != 0 && d1 == 0) wl = b[0][d0 - 1];
-            if constexpr (d0 == 0 && d1 != 0) wl = b[1][d1 - 1];
-            if constexpr (low != 0) u[low] = mul(u[low], wl);
-            static_for<1, (R + 15) / 16>([&](auto hc) {
-                constexpr int r = low + 16 * decltype(hc)::value;
-                if constexpr (r < R) {
-                    const float2 bh = b[2][decltype(hc)::value - 1];
-                    if constexpr (low != 0) {
-                        u[r] = mul(u[r], cmul(wl, bh));
-                    } else {
-                        u[r] = mul(u[r], bh);
-                    }
-                }
-            });
-        });
+        Dft<R, INV>::run_tw(u, pw);
     }
 }
 
@@ -379,6 +374,7 @@ __device__ __forceinline__ void run_stages(float2 (&v)[K::P], int t, int c, cons
                 const float2 w = L[(r - 1) * NS + k];
                 u[r] = INV ? cmulc(u[r], w) : cmul(u[r], w);
             });
+            Dft<R, INV>::run(u);
         } else if constexpr (NS > 1 && TwRegs<K, NS, R>::LATE) {
             // this butterfly's factors from the stage table, read now
             constexpr long long OFF = stage_table_offset(K::N, NS, R);
@@ -388,10 +384,12 @@ __device__ __forceinline__ void run_stages(float2 (&v)[K::P], int t, int c, cons
                 const float2 w = tw[OFF + (r - 1) * NS + k];
                 u[r] = INV ? cmulc(u[r], w) : cmul(u[r], w);
             });
+            Dft<R, INV>::run(u);
         } else if constexpr (NS > 1) {
-            tw_apply<K, NS, R, q, INV>(cur, u);
+            tw_dft<K, NS, R, q, INV>(cur, u);
+        } else {
+            Dft<R, INV>::run(u);
         }
-        Dft<R, INV>::run(u);
         static_for<0, R>([&](auto rc) { v[q + rc * B] = u[rc]; });
     });
     if constexpr (sizeof...(Rest) > 0) {

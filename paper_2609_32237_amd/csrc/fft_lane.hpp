@@ -110,8 +110,7 @@ __device__ __forceinline__ void lane_fft_1024(float2 (&v)[16], int lane, const f
     TwRegs<K, 256, 4> tw3;
     tw_issue<K, 256, 4>(tw3, base, tw);
     // stage 2: radix 16 on sub-transforms of length 16
-    tw_apply<K, 16, 16, 0, INV>(tw2, v);
-    Dft<16, INV>::run(v);
+    tw_dft<K, 16, 16, 0, INV>(tw2, v);
     // exchange: register bits 0..1 <-> lane bits 0..1
     lane_transpose_bit<0, 0>(v, lane);
     lane_transpose_bit<1, 1>(v, lane);
@@ -120,8 +119,7 @@ __device__ __forceinline__ void lane_fft_1024(float2 (&v)[16], int lane, const f
         constexpr int q = decltype(qc)::value;
         float2 u[4];
         static_for<0, 4>([&](auto rc) { u[rc] = v[4 * q + rc]; });
-        tw_apply<K, 256, 4, q, INV>(tw3, u);
-        Dft<4, INV>::run(u);
+        tw_dft<K, 256, 4, q, INV>(tw3, u);
         static_for<0, 4>([&](auto rc) { v[4 * q + rc] = u[rc]; });
     });
 }
