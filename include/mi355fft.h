@@ -219,11 +219,11 @@ size_t sar_workspace_bytes(int64_t n_az, int64_t n_rg, int inter_storage);
  *                   n_az == n_rg: the range pass, whose first workgroups
  *                   compute both reference spectra, and the azimuth pass.
  *                   Otherwise the azimuth reference spectrum takes a launch
- *                   of its own first (three).  For n_az of 8192 or 16384
- *                   with FP32 intermediates the azimuth pass runs as three
- *                   passes of short columns after a launch of both spectra
- *                   (five; `out` then also holds the range-compressed image
- *                   between the passes).
+ *                   of its own first (three).  For n_az of 16384 and
+ *                   n_rg of 4096 or more with FP32 intermediates the azimuth
+ *                   pass runs as three passes of short columns after a
+ *                   launch of both spectra (five; `out` then also holds the
+ *                   range-compressed image between the passes).
  *
  * Computes, with H_r = FFT(range_ref) and H_a = FFT(az_ref):
  *   y[a, :]   = IFFT( FFT(raw[a, :]) * conj(H_r) ) / n_rg      (pass 1, rows)

@@ -36,8 +36,8 @@ struct Configs<64> {
     using Cols = KList<KCfg<64, 16, 64, true, XCHG_SPLIT, 1, false, Radices<16, 4>>>;
     using Rcmc = Rows;
     using RowsHalf = Rows;
-    static constexpr int kRowDefault[2] = {0, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {0, 0};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<128> {
@@ -45,28 +45,30 @@ struct Configs<128> {
     using Cols = KList<KCfg<128, 16, 32, true, XCHG_SPLIT, 1, false, Radices<16, 8>>>;
     using Rcmc = Rows;
     using RowsHalf = Rows;
-    static constexpr int kRowDefault[2] = {0, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {0, 0};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<256> {
     using Rows = KList<KCfg<256, 16, 16, false, XCHG_SPLIT, 1, false, Radices<16, 16>>>;
-    using Cols = KList<KCfg<256, 16, 16, true, XCHG_SPLIT, 1, false, Radices<16, 16>>>;
+    using Cols = KList<KCfg<256, 16, 16, true, XCHG_SPLIT, 1, false, Radices<16, 16>>,
+                       KCfg<256, 16, 32, true, XCHG_SPLIT, 1, false, Radices<16, 16>>>;
     using Rcmc = Rows;
     using RowsHalf = Rows;
-    static constexpr int kRowDefault[2] = {0, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {0, 0};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<512> {
     using Rows = KList<KCfg<512, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 2>>>;
-    // 16-column strips measured 5% faster than 8 in the four-step passes
-    using Cols = KList<KCfg<512, 16, 16, true, XCHG_SPLIT, 1, false, Radices<16, 16, 2>>,
-                       KCfg<512, 16, 8, true, XCHG_SPLIT, 1, false, Radices<16, 16, 2>>>;
+    // 32 points per thread in two stages: one exchange instead of two (the
+    // four-step passes of 2^25 points 106 + 104 against 112 + 106 us)
+    using Cols = KList<KCfg<512, 32, 16, true, XCHG_SPLIT, 1, false, Radices<32, 16>>,
+                       KCfg<512, 32, 32, true, XCHG_SPLIT, 1, false, Radices<32, 16>>>;
     using Rcmc = Rows;
     using RowsHalf = Rows;
-    static constexpr int kRowDefault[2] = {0, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {0, 0};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<1024> {
@@ -79,7 +81,9 @@ struct Configs<1024> {
                        // four transforms (waves) or one per workgroup
                        KCfg<1024, 16, 4, false, XCHG_LANE, 1, false, Radices<16, 16, 4>>,
                        KCfg<1024, 16, 1, false, XCHG_LANE, 1, false, Radices<16, 16, 4>>>;
-    using Cols = KList<KCfg<1024, 16, 8, true, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>,
+    // two stages, one exchange; 8 or 16 columns (64-byte pieces or whole lines in FP32)
+    using Cols = KList<KCfg<1024, 32, 8, true, XCHG_SPLIT, 1, false, Radices<32, 32>>,
+                       KCfg<1024, 32, 16, true, XCHG_SPLIT, 1, false, Radices<32, 32>>,
                        KCfg<1024, 16, 8, true, XCHG_FULL, 0, false, Radices<16, 16, 4>>>;
     // 8 range bins per strip: 229 against 256 us for 16 (which held one
     // Doppler bin per thread, too few for the column gather) on a 1024 x 16384
@@ -87,8 +91,8 @@ struct Configs<1024> {
     using Rcmc = KList<KCfg<1024, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>,
                        KCfg<1024, 16, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>>;
     using RowsHalf = KList<KCfg<1024, 16, 4, false, XCHG_HALF, 1, false, Radices<16, 16, 4>>>;
-    static constexpr int kRowDefault[2] = {1, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {1, 1}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {1, 0};
+    static constexpr int kRowMatched[2] = {1, 1};
 };
 template <>
 struct Configs<2048> {
@@ -98,6 +102,10 @@ struct Configs<2048> {
                        KCfg<2048, 16, 2, false, XCHG_FULL, 0, false, Radices<16, 16, 8>>,
                        KCfg<2048, 16, 1, false, XCHG_FULL, 1, false, Radices<16, 16, 8>>>;
     using Cols = KList<KCfg<2048, 16, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
+                       KCfg<2048, 16, 8, true, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
+                       // 64 points per thread: one exchange, whole lines with 16 columns
+                       KCfg<2048, 64, 8, true, XCHG_SPLIT, 1, false, Radices<64, 32>>,
+                       KCfg<2048, 64, 16, true, XCHG_SPLIT, 1, false, Radices<64, 32>>,
                        KCfg<2048, 16, 4, true, XCHG_FULL, 0, false, Radices<16, 16, 8>>>;
     // 32 points per thread: 228 against 241 us (16 points, 8 range bins) and
     // 247 us (16 points, 4 range bins) for a 2048 x 8192 range-Doppler chain
@@ -105,8 +113,8 @@ struct Configs<2048> {
     using Rcmc = KList<KCfg<2048, 32, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
                        KCfg<2048, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>>;
     using RowsHalf = KList<KCfg<2048, 16, 2, false, XCHG_HALF, 1, false, Radices<16, 16, 8>>>;
-    static constexpr int kRowDefault[2] = {0, 0}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {0, 0};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<4096> {
@@ -159,8 +167,8 @@ struct Configs<4096> {
     // inputs that no cache holds, an FP32 chain takes 145 us with 8 columns
     // and 157 with 4 (FP16 124 and 128); a single chain after a flush, where
     // the intermediate is still in the Infinity Cache, 141 and 135.
-    static constexpr int kRowDefault[2] = {8, 1}, kColDefault[2] = {5, 5};
-    static constexpr int kRowMatched[2] = {1, 9}, kColMatched[2] = {5, 5};
+    static constexpr int kRowDefault[2] = {8, 1};
+    static constexpr int kRowMatched[2] = {1, 9};
 };
 template <>
 struct Configs<8192> {
@@ -173,7 +181,10 @@ struct Configs<8192> {
                        KCfg<8192, 16, 1, false, XCHG_SPLIT, 2, false, Radices<16, 16, 16, 2>>,
                        // the second stage's 240 factors from LDS (twiddle mode 3)
                        KCfg<8192, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 2>>>;
-    using Cols = KList<KCfg<8192, 32, 2, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 2>>,
+    // three stages; 4 columns hold a CU (64 or 32 points per thread), 2 columns half
+    using Cols = KList<KCfg<8192, 64, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
+                       KCfg<8192, 32, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
+                       KCfg<8192, 32, 2, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
                        KCfg<8192, 32, 2, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16, 2>>>;
     using Rcmc = KList<KCfg<8192, 32, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 2>>,
                        KCfg<8192, 16, 2, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 2>>>;
@@ -183,8 +194,8 @@ struct Configs<8192> {
     // FP16: 32 points per thread in three stages, 5.7 vs 4.9 TB/s.  FP32:
     // the second stage's factors from LDS, 5,740 against 5,607 GB/s flushed
     // and 5,700-5,731 against 5,318-5,604 back to back (same box, one run)
-    static constexpr int kRowDefault[2] = {7, 4}, kColDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0}, kColMatched[2] = {0, 0};
+    static constexpr int kRowDefault[2] = {7, 4};
+    static constexpr int kRowMatched[2] = {0, 0};
 };
 template <>
 struct Configs<16384> {
@@ -196,14 +207,15 @@ struct Configs<16384> {
                        KCfg<16384, 32, 1, false, XCHG_SPLIT, 2, false, Radices<32, 16, 32>>,
                        // the second stage's 240 factors from LDS (twiddle mode 3)
                        KCfg<16384, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 4>>>;
-    using Cols = KList<KCfg<16384, 32, 1, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16, 4>>,
-                       KCfg<16384, 32, 1, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 4>>>;
+    using Cols = KList<KCfg<16384, 32, 2, true, XCHG_SPLIT, 1, false, Radices<32, 16, 32>>,
+                       KCfg<16384, 32, 1, true, XCHG_SPLIT, 1, false, Radices<32, 16, 32>>,
+                       KCfg<16384, 32, 1, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16, 4>>>;
     // three stages (32 x 16 x 32) against four: one exchange and one twiddle
     // pass fewer; measured 5.5 vs 5.3 TB/s (FP32) and 4.9 vs 3.8 TB/s (FP16).
     // FP32: four stages with the second stage's factors from LDS beat both,
     // 5,800-5,816 against 5,660-5,693 GB/s flushed and 5,637-5,828 against
     // 5,128-5,722 back to back (two boxes, same process each)
-    static constexpr int kRowDefault[2] = {6, 4}, kColDefault[2] = {1, 1};
+    static constexpr int kRowDefault[2] = {6, 4};
     using Rcmc = KList<KCfg<16384, 32, 2, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 4>>,
                        KCfg<16384, 16, 1, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 4>>>;
     // binary16 exchange: three stages fastest (4.8 TB/s), then 32 points per
@@ -211,7 +223,7 @@ struct Configs<16384> {
     using RowsHalf = KList<KCfg<16384, 32, 1, false, XCHG_HALF, 1, false, Radices<32, 16, 32>>,
                            KCfg<16384, 32, 1, false, XCHG_HALF, 1, false, Radices<16, 16, 16, 4>>,
                            KCfg<16384, 16, 1, false, XCHG_HALF, 1, false, Radices<16, 16, 16, 4>>>;
-    static constexpr int kRowMatched[2] = {4, 4}, kColMatched[2] = {1, 1};
+    static constexpr int kRowMatched[2] = {4, 4};
 };
 
 // Small batches: a batch that gives the default row shape (several
@@ -235,62 +247,60 @@ struct SmallRows<2048> {
     static constexpr long long below = 2 * 256;
 };
 
-// Few columns: the 8-column strips of 4096 points fill a CU each, so 1024
-// columns or fewer leave half of the 256 CUs idle; 4-column strips of 16
-// points per thread (1024 threads) use twice as many CUs with twice the waves.
-// Measured, plain transform: 250 columns 14.8 against 19.0 us (FP32) and 12.4
-// against 15.8 (FP16), 512 columns 16.4 / 21.3, 1000 columns 18.1 / 19.2, but
-// 1536 columns 46.9 / 32.0; SAR chain of 4096 x 1024 52.5 / 56.9 (FP16
-// intermediate 44.6 / 51.6).
+// The column shape of a pass over `columns` columns in all (every problem of
+// the grid counted), by what the pass does:
+//   plain    the transform (and the last pass of the split forms);
+//   twiddled the four-step epilogues (at most 32 points per thread);
+//   scaled   the range-Doppler chain's azimuth pass, written transposed;
+//   matched  the SAR azimuth pass (two transforms).
+// half: FP16 storage on either side.  Wider strips read and write longer
+// pieces of each row (whole 128-byte lines at 16 FP32 columns) and pay once
+// there are strips enough for the 256 CUs; with fewer columns narrow strips
+// keep more CUs busy.  Times in us, narrower against wider shape, on inputs
+// that no cache holds:
+//   256   pass of 16384 columns 12.7 / 14.2 (16 / 32 columns a strip), of
+//         65536 55.3 / 53.8 and, in FP16, 38.7 / 34.1
+//   512   16384 columns 30.2 / 26.9 (FP16 17.9 / 18.8), 65536 FP16 73.2 / 70.3
+//   1024  4096 columns 14.1 / 14.3, 8192 38.3 / 30.3, 16384 81.9 / 67.9 (FP16
+//         48.7 / 41.9); SAR over 8192 columns 78.1 / 80.1, 16384 162.5 / 154.3
+//   2048  (4, 8 and twice 16 points; 8 and 16 columns with 64 points) 1000
+//         columns 11.3, 11.9, 12.9, 17.0; 2048 17.5, 15.8, 16.8, 20.3; 4096
+//         59.8, 43.6, 39.6, 29.2 (FP16 25.9, 20.0, 18.1, 19.6); 8192 143, 104,
+//         83.4, 57.6; 16384 356, 233, 177, 156 (FP16 191, 164, 106, 82.3);
+//         SAR over 1024 32.1, 35.2, 39.2, 43.8; 4096 93.5, 74.8, 76.2, 80.4
+//         (FP16 86.7, 69.7, 66.2, 72.4), 8192 209, 167, 154, 157
+//   4096  250 columns 14.8 (4 columns, 1024 threads) / 19.0 (8 columns, 64
+//         points), 1000 18.1 / 19.2, 1536 46.9 / 32.0; SAR over 1024 columns
+//         52.5 / 56.9, over 4096 157 (4 columns, 64 points) / 145
+//   8192  in place: 100 columns 20.6 / 23.0 (2 / 4 columns), 1000 61.3 / 41.9
+//         (44.1 with 64 points), 4096 332 / 248 (234); SAR over 1024 98.0 /
+//         95.8 (94.5), 2048 238 / 194 (177); range-Doppler FP32 238 / 244
+//   16384 in place: 100 columns 35.6 / 36.6 (1 / 2), 1000 212 / 123; SAR over
+//         1024 266 / 202, range-Doppler 298 / 278
+enum { COLS_PLAIN, COLS_TWIDDLED, COLS_SCALED, COLS_MATCHED };
 template <int N>
-struct SmallCols {
-    static constexpr int variant = -1;      // index into Cols, or none
-    static constexpr long long most = 0;    // applies to this many columns or fewer
-};
-template <>
-struct SmallCols<4096> {
-    static constexpr int variant = 2;
-    static constexpr long long most = 4 * 256;
-};
-
-template <int I, class L>
-struct KAt;
-template <class K, class... Ks>
-struct KAt<0, KList<K, Ks...>> {
-    using type = K;
-};
-template <int I, class K, class... Ks>
-struct KAt<I, KList<K, Ks...>> {
-    using type = typename KAt<I - 1, KList<Ks...>>::type;
-};
-
-// Column shapes for the four-step epilogues (EPI_TWIDDLE, EPI_TWIDDLE_Y,
-// EPI_MATCHED_Y), which hold at most 32 points per thread: the size's default
-// shapes unless a size names others.
-template <int N>
-struct FourStepCols {
-    static constexpr int plain[2] = {Configs<N>::kColDefault[0], Configs<N>::kColDefault[1]};
-    static constexpr int matched = Configs<N>::kColMatched[0];  // (FP32 data only)
-};
-template <>
-struct FourStepCols<4096> {
-    static constexpr int plain[2] = {3, 3};
-    static constexpr int matched = 3;
-};
-
-// The column shape of the scaled transform (EPI_SCALE, the range-Doppler
-// chain's azimuth pass).  At 4096 points the 4-column radix-64 strips
-// measured 205.7 against 214.3 us (8 columns) per range-Doppler chain with
-// FP32 intermediates, 190.7 against 191.9 with FP16 (30 interleaved flushed
-// samples each), although 8 columns are faster for the plain transform.
-template <int N>
-struct ScaleCols {
-    static constexpr int v[2] = {Configs<N>::kColDefault[0], Configs<N>::kColDefault[1]};
-};
-template <>
-struct ScaleCols<4096> {
-    static constexpr int v[2] = {6, 6};
-};
+constexpr int column_shape(int use, int half, long long columns) {
+    if (N == 256 || N == 512) return columns >= 32768 ? 1 : 0;
+    if (N == 1024) return columns >= (use == COLS_MATCHED ? 16384 : 8192) ? 1 : 0;
+    if (N == 2048) {
+        if (columns < 2048 || (use == COLS_SCALED && columns < 4096)) return 0;
+        if (columns < 4096 || use == COLS_TWIDDLED) return 1;
+        if (use == COLS_PLAIN) return half && columns < 8192 ? 2 : 3;
+        return half || columns >= 8192 ? 2 : 1;
+    }
+    if (N == 4096) {
+        if (use == COLS_TWIDDLED) return 3;
+        if (use == COLS_SCALED) return 6;  // 4 columns: written transposed, 206 against 214 us (8 columns) per chain
+        return columns <= 1024 ? 2 : 5;
+    }
+    if (N == 8192) {
+        if (use == COLS_SCALED) return half ? 1 : 2;
+        if (use == COLS_PLAIN && columns < 512) return 2;
+        return half || (use == COLS_PLAIN && columns <= 1024) ? 1 : 0;
+    }
+    if (N == 16384) return use == COLS_PLAIN && columns < 256 ? 1 : 0;
+    return 0;
+}
 
 template <class L>
 struct KListSize;
@@ -446,22 +456,12 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
         return with_variant(v, typename Configs<N>::Rows{}, f);
     }
     using Cols = typename Configs<N>::Cols;
-    static_assert(KAt<FourStepCols<N>::plain[0], Cols>::type::P <= 32 &&
-                      KAt<FourStepCols<N>::plain[1], Cols>::type::P <= 32 &&
-                      KAt<FourStepCols<N>::matched, Cols>::type::P <= 32,
-                  "the four-step epilogues hold at most 32 points per thread");
-    const bool four_step = epi == EPI_TWIDDLE || epi == EPI_TWIDDLE_Y || epi == EPI_MATCHED_Y;
-    int v = variant;
-    if (v < 0) {
-        if (four_step) {
-            v = mf ? FourStepCols<N>::matched : FourStepCols<N>::plain[half];
-        } else if (epi == EPI_SCALE) {
-            v = ScaleCols<N>::v[half];
-        } else {
-            v = mf ? Configs<N>::kColMatched[half] : Configs<N>::kColDefault[half];
-            if (a.batch <= SmallCols<N>::most) v = SmallCols<N>::variant;
-        }
-    }
+    const long long columns = a.batch * (a.outer > 1 ? a.outer : 1) * (a.outer2 > 1 ? a.outer2 : 1);
+    const int use = epi == EPI_NONE      ? COLS_PLAIN
+                    : epi == EPI_SCALE   ? COLS_SCALED
+                    : epi == EPI_MATCHED ? COLS_MATCHED
+                                         : COLS_TWIDDLED;
+    const int v = variant >= 0 ? variant : column_shape<N>(use, half, columns);
     return with_variant(v, Cols{}, f);
 }
 

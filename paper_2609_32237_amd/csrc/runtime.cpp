@@ -713,11 +713,14 @@ size_t sar_workspace_bytes(int64_t n_az, int64_t n_rg, int inter_storage) {
     return spectra + kChainFlagBytes + (size_t)n_az * (size_t)n_rg * el;
 }
 
-// An azimuth pass over 8192- or 16384-point columns holds one or two columns
-// per workgroup (8- or 16-byte pieces of each row).  With FP32 intermediates
-// it runs instead as three passes of short columns in the four-step form
-// (n_az = n1 * n2, n1 = 128, j = n2 j1 + j2, k = k1 + n1 k2), each reading
-// and writing wide pieces of the rows:
+// An azimuth pass over 16384-point columns holds two columns per workgroup
+// (16-byte pieces of each row).  With FP32 intermediates and rows of 4096
+// points or more it runs instead as three passes of short columns in the
+// four-step form (n_az = n1 * n2, n1 = 128, j = n2 j1 + j2, k = k1 + n1 k2),
+// each reading and writing wide pieces of the rows.  Measured, three passes
+// against one: 16384 x 4096 859 / 898 us, x 8192 1775 / 1778, but x 2048 436 /
+// 414 and x 1024 218 / 202; 8192 pulses (four columns a workgroup) x 1024 117
+// / 94, x 2048 210 / 177, x 4096 435 / 388, x 8192 886 / 810.
 //   B1  for each j2: 128-point FFTs down rows n2 j1 + j2, output k1 times
 //       W^(j2 k1), to rows j2 n1 + k1 of the workspace;
 //   B2  in place, for each k1: n2-point FFT down rows j2 n1 + k1 (giving
@@ -727,10 +730,10 @@ size_t sar_workspace_bytes(int64_t n_az, int64_t n_rg, int inter_storage) {
 //       row n2 j1 + j2 of the image.
 // The range pass then writes its result into `out`, which B1 reads.  A forced
 // column shape (MI355FFT_COL_VARIANT) keeps the single column pass.
-static bool long_azimuth(int64_t n_az, int inter_storage) {
+static bool long_azimuth(int64_t n_az, int64_t n_rg, int inter_storage) {
     const char *cv = std::getenv("MI355FFT_COL_VARIANT");
     if (cv && cv[0]) return false;
-    return inter_storage == FFT_STORAGE_FP32 && (n_az == 8192 || n_az == 16384);
+    return inter_storage == FFT_STORAGE_FP32 && n_az == 16384 && n_rg >= 4096;
 }
 
 }  // extern "C"
@@ -839,7 +842,7 @@ int sar_run(int64_t n_az, int64_t n_rg, int inter_storage, const void *raw, cons
         return err;
     };
 
-    if (long_azimuth(n_az, inter_storage)) {
+    if (long_azimuth(n_az, n_rg, inter_storage)) {
         e = separate_references(true, true);
         if (e != hipSuccess) return map_hip(e);
         return sar_long_azimuth(n_az, n_rg, raw, out, mid, h_rg, h_az, t, vrow, stream);
@@ -886,23 +889,20 @@ int sar_run(int64_t n_az, int64_t n_rg, int inter_storage, const void *raw, cons
 }
 
 // The allocation-free SAR entry point's fixed device array (noalloc.hip):
-// the twiddle tables of every length 64 ... 16384 and the two-level tables of
-// 8192 and 16384, filled once per device, then the chain's workspace.
-constexpr size_t na_tw_entries_below(int64_t n) {  // tables of the lengths 64 .. n / 2
+// the twiddle tables of every length 1024 ... 16384, filled once per device,
+// then the chain's workspace.
+constexpr size_t na_tw_entries_below(int64_t n) {  // tables of the lengths 1024 .. n / 2
     size_t e = 0;
-    for (int64_t m = 64; m < n; m *= 2) e += (size_t)mi355fft::twiddle_entries(m);
+    for (int64_t m = 1024; m < n; m *= 2) e += (size_t)mi355fft::twiddle_entries(m);
     return e;
 }
-constexpr size_t kNaTwBytes = na_tw_entries_below(32768) * sizeof(float2);  // lengths 64 .. 16384
-constexpr size_t kNaFtabOffset = kNaTwBytes;
-constexpr size_t kNaFtabBytes = (size_t)(192 + 256) * sizeof(float2);  // 8192: 128 + 64; 16384: 128 + 128
-constexpr size_t kNaWorkspaceOffset = mi355fft::round_up_256(kNaFtabOffset + kNaFtabBytes);
+constexpr size_t kNaTwBytes = na_tw_entries_below(32768) * sizeof(float2);  // lengths 1024 .. 16384
+constexpr size_t kNaWorkspaceOffset = mi355fft::round_up_256(kNaTwBytes);
 static_assert(kNaWorkspaceOffset + 2 * 16384 * sizeof(float2) + kChainFlagBytes + mi355fft::kNoallocMaxImageBytes <=
                   mi355fft::kNoallocScratchBytes,
               "the fixed array holds the tables, both spectra, the flag and the largest intermediate");
 
 size_t na_tw_offset(int64_t n) { return na_tw_entries_below(n) * sizeof(float2); }
-size_t na_ftab_offset(int64_t n) { return kNaFtabOffset + (n == 8192 ? 0 : 192 * sizeof(float2)); }
 
 std::mutex g_na_mutex;
 std::map<int, char *> g_na;  // device -> its array, tables filled
@@ -923,15 +923,11 @@ int noalloc_base(int device, char **base) {
     if (e != hipSuccess) return map_hip(e);
     char *b = static_cast<char *>(p);
     std::vector<float2> host, all;
-    for (int64_t n = 64; n <= 16384; n *= 2) {
+    for (int64_t n = 1024; n <= 16384; n *= 2) {
         host_twiddles(n, host);
         all.insert(all.end(), host.begin(), host.end());
     }
-    for (int64_t n : {int64_t(8192), int64_t(16384)}) {
-        host_fourstep_table(n, (ilog2(n) + 1) / 2, host);
-        all.insert(all.end(), host.begin(), host.end());
-    }
-    if (all.size() * sizeof(float2) != kNaTwBytes + kNaFtabBytes) return FFT_EINVAL;  // layout mismatch
+    if (all.size() * sizeof(float2) != kNaTwBytes) return FFT_EINVAL;  // layout mismatch
     e = hipMemcpy(b, all.data(), all.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e != hipSuccess) return map_hip(e);
     g_na[device] = b;
@@ -962,7 +958,7 @@ int sar_form_image_ex(int64_t n_az, int64_t n_rg, int inter_storage, const void 
     SarTables t{};
     rc = get_twiddles(device, n_rg, &t.tw_rg);
     if (rc == FFT_OK) rc = get_twiddles(device, n_az, &t.tw_az);
-    if (rc == FFT_OK && long_azimuth(n_az, inter_storage)) {
+    if (rc == FFT_OK && long_azimuth(n_az, n_rg, inter_storage)) {
         rc = get_twiddles(device, 128, &t.tw1);
         if (rc == FFT_OK) rc = get_twiddles(device, n_az / 128, &t.tw2);
         if (rc == FFT_OK) rc = get_fourstep_table(device, n_az, (ilog2(n_az) + 1) / 2, &t.ftab);
@@ -994,12 +990,8 @@ int sar_form_image_noalloc(int64_t n_az, int64_t n_rg, int inter_storage, const 
     if (overlaps(range_ref, (size_t)n_rg * 8, ws, wsb) || overlaps(az_ref, (size_t)n_az * 8, ws, wsb))
         return FFT_EINVAL;
     auto tw = [&](int64_t n) { return reinterpret_cast<const float2 *>(base + na_tw_offset(n)); };
-    SarTables t{tw(n_rg), tw(n_az), nullptr, nullptr, nullptr};
-    if (long_azimuth(n_az, inter_storage)) {
-        t.tw1 = tw(128);
-        t.tw2 = tw(n_az / 128);
-        t.ftab = reinterpret_cast<const float2 *>(base + na_ftab_offset(n_az));
-    }
+    // (images of the long-azimuth form, 16384 x 4096 and more, exceed the array)
+    const SarTables t{tw(n_rg), tw(n_az), nullptr, nullptr, nullptr};
     return sar_run(n_az, n_rg, inter_storage, raw, range_ref, az_ref, out, ws, t, stream);
 } catch (const std::bad_alloc &) {
     return FFT_ENOMEM;

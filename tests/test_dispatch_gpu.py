@@ -26,29 +26,86 @@ def api():
     return torch_api
 
 
-def run_columns(api, n, count, pad, storage, direction=-1):
-    """The first `count` columns of an n x (count + pad) matrix, and the oracle's."""
+def run_columns(api, n, count, pad, storage, direction=-1, in_place=False):
+    """The first `count` columns of an n x (count + pad) matrix, and the
+    oracle's: all of them, or the first, the last and 14 more."""
     import torch
 
     x = workloads.uniform_complex(n, count + pad, 31 + count, "fp16" if storage else "fp32")
     xd = to_dev(x)
-    out = torch.full_like(xd, 7.0)
+    out = xd if in_place else torch.full_like(xd, 7.0)
     plan = api.Plan(n, count, count + pad, 1, storage, direction)
     plan.execute(xd, out)
     torch.cuda.synchronize()
     plan.close()
-    got = widen(to_host(out))
-    assert np.all(got[:, count:] == (7.0 + 7.0j if storage else 7.0)), "columns outside the batch were written"
-    ref = oracle.fft(np.ascontiguousarray(np.moveaxis(x[:, :count], 0, 1)), direction)
-    return got[:, :count].T, ref
+    y = to_host(out)
+    outside = x[:, count:] if in_place else np.full_like(x[:, count:], 7.0)
+    assert np.array_equal(y[:, count:], outside), "columns outside the batch were written"
+    pick = np.arange(count) if count <= 32 else np.unique(
+        np.r_[0, count - 1, np.random.default_rng(count).integers(0, count, 14)])
+    ref = oracle.fft(np.ascontiguousarray(np.moveaxis(x[:, pick], 0, 1)), direction)
+    return np.ascontiguousarray(widen(np.ascontiguousarray(y[:, pick])).T), ref
 
 
 @pytest.mark.parametrize("storage", [0, 1])
-@pytest.mark.parametrize("count,pad", [(1, 0), (5, 3), (1023, 1), (1024, 0), (1025, 2)])
-def test_few_columns_of_4096(api, storage, count, pad):
-    """Up to 1024 columns of 4096 points take the 4-column strips, more the
-    8-column ones; a strip's last columns may be missing."""
-    got, ref = run_columns(api, 4096, count, pad, storage)
+@pytest.mark.parametrize("n,count,pad", [(1024, 3, 2), (1024, 8191, 1), (1024, 8192, 0),
+                                         (2048, 2047, 3), (2048, 2049, 0), (2048, 4095, 1), (2048, 4100, 0),
+                                         (2048, 8191, 1), (2048, 8193, 0),
+                                         (4096, 1, 0), (4096, 5, 3), (4096, 1023, 1), (4096, 1024, 0), (4096, 1025, 2)])
+def test_columns_by_count(api, storage, n, count, pad):
+    """The strip width (4, 8 or 16 columns) goes with the number of columns;
+    a strip's last columns may be missing."""
+    got, ref = run_columns(api, n, count, pad, storage)
     e = rel_rows(got, ref).max()
-    log(f"columns 4096 x {count} storage {storage}: rel {e:.2e}")
+    log(f"columns {n} x {count} storage {storage}: rel {e:.2e}")
     assert e < TOL[storage]
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("n,count", [(8192, 1), (8192, 511), (8192, 514), (8192, 1025), (16384, 3), (16384, 255),
+                                     (16384, 257)])
+def test_long_columns_in_place(api, storage, n, count):
+    """8192 and 16384 points in place: single passes of 1, 2 or 4 columns."""
+    got, ref = run_columns(api, n, count, 1, storage, 1, True)
+    e = rel_rows(got, ref).max()
+    log(f"columns in place {n} x {count} storage {storage}: rel {e:.2e}")
+    assert e < TOL[storage]
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("log2n,batch", [(16, 127), (16, 128), (18, 63), (18, 65), (20, 7), (20, 8), (21, 1), (21, 2)])
+def test_long_transforms_by_batch(api, storage, log2n, batch):
+    """The four-step passes' strips go with the columns of all transforms."""
+    import torch
+
+    n = 1 << log2n
+    x = workloads.uniform_complex(batch, n, 77 + batch, "fp16" if storage else "fp32")
+    xd = to_dev(x)
+    plan = api.Plan(n, batch, 1, n, storage, -1, log2n // 2 if storage else 0)
+    y = plan.execute(xd, torch.empty_like(xd))
+    torch.cuda.synchronize()
+    plan.close()
+    pick = np.unique([0, batch // 2, batch - 1])
+    got = widen(to_host(y[torch.from_numpy(pick).cuda()]))
+    ref = oracle.fft(x[pick]) * (2.0 ** -(log2n // 2) if storage else 1.0)
+    e = rel_rows(got, ref).max()
+    log(f"long 2^{log2n} x {batch} storage {storage}: rel {e:.2e}")
+    assert e < TOL[storage]
+
+
+@pytest.mark.parametrize("inter", [0, 1])
+@pytest.mark.parametrize("shape", [(2048, 8192), (1024, 8192), (16384, 4096)])
+def test_images_by_shape(api, shape, inter):
+    """Azimuth passes whose strips or form go with the image's width (the
+    three-pass form at 16384 x 4096 with an FP32 intermediate)."""
+    n_az, n_rg = shape
+    sc = workloads.sar_scene(n_az=n_az, n_rg=n_rg, n_targets=4, len_rg=256, len_az=128, sigma=0.0, seed=3, min_sep=24)
+    import torch
+
+    img = to_host(api.sar_form_image(to_dev(sc.raw), to_dev(sc.range_ref), to_dev(sc.az_ref), inter))
+    torch.cuda.synchronize()
+    ref = oracle.sar_chain(sc.raw, sc.range_ref, sc.az_ref)
+    img -= ref.astype(np.complex64)
+    e = np.linalg.norm(img) / np.linalg.norm(ref)
+    log(f"sar {n_az}x{n_rg} inter {inter}: rel {e:.2e}")
+    assert e < TOL[inter]
