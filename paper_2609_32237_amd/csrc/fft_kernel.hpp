@@ -36,7 +36,11 @@
 //          FP32 operations than 1, more loads, each one coalesced);
 //          3: stages whose own table is small (at most kLdsTwEntries
 //          factors) read every factor from a copy of that table in LDS, which
-//          the workgroup fills once; the other stages work as in mode 1.
+//          the workgroup fills once; the other stages work as in mode 1;
+//          4: as mode 1, but every power of two is read, from the stage's own
+//          table (consecutive lanes, consecutive entries): fewest operations
+//          and least rounding error (4096 points 1.46e-7 against 1.50e-7),
+//          two more reads per butterfly.
 //   PERSIST the workgroup loops over its share of the batch and loads the
 //          next transform into a second register array while it computes the
 //          current one (the second-array idea of Section VI, used here to
@@ -197,7 +201,7 @@ struct TwRegs {
     // butterflies per thread, 62 at radix 32, either of which spills.  Those
     // stages read each butterfly's factors just before applying them instead.
     static constexpr bool LATE = MODE == 2 && (B > 1 || R >= 32);
-    static constexpr int LOADS = NS == 1 || LATE || MODE == 3 ? 0 : (MODE == 1 ? num_digits4(R) : R - 1);
+    static constexpr int LOADS = NS == 1 || LATE || MODE == 3 ? 0 : (MODE == 1 ? num_digits4(R) : MODE == 4 ? ilog2(R) : R - 1);
     float2 w[B][LOADS > 0 ? LOADS : 1];
 };
 
@@ -221,6 +225,14 @@ __device__ __forceinline__ void tw_issue(TwRegs<K, NS, R> &tr, int t, const floa
                 static_for<1, R>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
                     tr.w[q][r - 1] = tw[OFF + (r - 1) * NS + k];
+                });
+            } else if constexpr (TwRegs<K, NS, R>::MODE == 4) {
+                // W^(k 2^i) is row 2^i - 1 of the stage's table
+                static_assert(R <= 32, "stage tables reach radix 32");
+                constexpr long long OFF = stage_table_offset(K::N, NS, R);
+                static_for<0, ilog2(R)>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    tr.w[q][i] = tw[OFF + ((1 << i) - 1) * NS + k];
                 });
             } else {
                 static_for<0, TwRegs<K, NS, R>::LOADS>([&](auto ic) {
@@ -251,15 +263,17 @@ __device__ __forceinline__ float2 unit_square(float2 w) {
 // r = 0..R-1.  With the digit-base reads (TWMODE 1) the layers of the
 // decimation in time need only the powers W^(k 2^i): the even ones are read,
 // the odd ones their squares (reading all of them was 2-6% slower on the
-// issue-bound kernels: 16384 FP16 rows 425-436 against 437-447 us).  The other
-// modes multiply first.
+// issue-bound kernels: 16384 FP16 rows 425-436 against 437-447 us; mode 4 does
+// so where memory is the bound).  The other modes multiply first.
 // Against multiplying every input by its own factor (formed by up to three
 // products) and a radix-4 butterfly, VALU instructions per point fall from
 // 44 to 37 at 4096 points, at 2% less rounding error (relative to FP64,
 // 4096 points: 1.50e-7 against 1.53e-7).
 template <class K, int NS, int R, int q, bool INV>
 __device__ __forceinline__ void tw_dft(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
-    if constexpr (TwRegs<K, NS, R>::MODE != 1) {
+    if constexpr (TwRegs<K, NS, R>::MODE == 4) {
+        Dft<R, INV>::run_tw(u, tr.w[q]);
+    } else if constexpr (TwRegs<K, NS, R>::MODE != 1) {
         static_for<1, R>([&](auto rc) { u[rc] = INV ? cmulc(u[rc], tr.w[q][rc - 1]) : cmul(u[rc], tr.w[q][rc - 1]); });
         Dft<R, INV>::run(u);
     } else {
