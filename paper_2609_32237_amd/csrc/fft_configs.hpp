@@ -91,8 +91,11 @@ struct Configs<1024> {
     using Rcmc = KList<KCfg<1024, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>,
                        KCfg<1024, 16, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>>;
     using RowsHalf = KList<KCfg<1024, 16, 4, false, XCHG_HALF, 1, false, Radices<16, 16, 4>>>;
-    static constexpr int kRowDefault[2] = {1, 0};
-    static constexpr int kRowMatched[2] = {1, 1};
+    // one transform, one wave, per workgroup (no barrier waits): FP16 47.8
+    // against 51.4 us for 2^25 points, FP32 89.0 / 89.2; matched, SAR 1024 x
+    // 1024 21.0 / 21.9 us, 4096 x 1024 50.4 / 51.2
+    static constexpr int kRowDefault[2] = {4, 4};
+    static constexpr int kRowMatched[2] = {4, 4};
 };
 template <>
 struct Configs<2048> {
@@ -113,8 +116,11 @@ struct Configs<2048> {
     using Rcmc = KList<KCfg<2048, 32, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
                        KCfg<2048, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>>;
     using RowsHalf = KList<KCfg<2048, 16, 2, false, XCHG_HALF, 1, false, Radices<16, 16, 8>>>;
-    static constexpr int kRowDefault[2] = {0, 0};
-    static constexpr int kRowMatched[2] = {0, 0};
+    // FP32: one transform per workgroup (88.5 against 91.4 us for 2^25 points,
+    // 20.1 / 20.6 for 2^23; FP16 50.4 / 52.2 but 14.2 / 13.7), matched too (SAR
+    // 4096 x 2048 81.6 / 85.4 us, FP16 76.6 / 74.6)
+    static constexpr int kRowDefault[2] = {4, 0};
+    static constexpr int kRowMatched[2] = {4, 0};
 };
 template <>
 struct Configs<4096> {
@@ -158,19 +164,18 @@ struct Configs<4096> {
     // FP32 rows: with the rows' XCD groups, streaming stores win back to back
     // (6,108-6,171 against 6,015-6,027 GB/s, same process; flushed 6,120
     // against 6,298, where a call without them leaves its write-back for later)
-    // matched rows with an FP16 intermediate (issue-bound): the LDS factors
-    // took the range-Doppler chain 0.4-2.8 us faster in five same-process
-    // comparisons on two boxes (181.2 -> 179.0 us on one), and moved the SAR
-    // chain by -0.4 to +1.4 us; with an FP32 intermediate they cost the SAR
-    // chain 1.6-2.7 us, so those rows keep the computed factors
+    // FP16 rows: the second stage's factors from LDS, 13.5 against 15.2 us for
+    // 2^23 points, 47.9 / 53.3 for 2^25
+    // matched rows: the same for the SAR chain (142.3-143.1 against 146.9-148.3
+    // us, FP16 125.4-126.1 / 125.5-125.8), not for the range-Doppler one (RdRows)
     // matched columns (the SAR azimuth pass): bound by the 64-byte pieces of
     // the image rows (128 MiB strided reads alone take 34 us, writes 24 us);
     // the 4-column strips' 32-byte pieces cost more.  Image after image, on
     // inputs that no cache holds, an FP32 chain takes 145 us with 8 columns
     // and 157 with 4 (FP16 124 and 128); a single chain after a flush, where
     // the intermediate is still in the Infinity Cache, 141 and 135.
-    static constexpr int kRowDefault[2] = {8, 1};
-    static constexpr int kRowMatched[2] = {1, 9};
+    static constexpr int kRowDefault[2] = {8, 9};
+    static constexpr int kRowMatched[2] = {9, 9};
 };
 template <>
 struct Configs<8192> {
@@ -197,7 +202,9 @@ struct Configs<8192> {
     // the second stage's factors from LDS, 5,740 against 5,607 GB/s flushed
     // and 5,700-5,731 against 5,318-5,604 back to back (same box, one run)
     static constexpr int kRowDefault[2] = {7, 4};
-    static constexpr int kRowMatched[2] = {0, 0};
+    // matched: three stages too (SAR 1024 x 8192 75.1 against 80.9 us and, with
+    // an FP16 intermediate, 68.4 against 72.3; range-Doppler 101.8 / 106.9)
+    static constexpr int kRowMatched[2] = {4, 4};
 };
 template <>
 struct Configs<16384> {
@@ -228,25 +235,46 @@ struct Configs<16384> {
     static constexpr int kRowMatched[2] = {4, 4};
 };
 
-// Small batches: a batch that gives the default row shape (several
-// transforms per workgroup) fewer workgroups than the chip has CUs runs one
-// transform per workgroup instead.  Measured on MI355X for 64 transforms
-// (one flushed call): N = 1024 6.7 against 7.7 us, N = 2048 7.3 against
-// 8.1 us.
+// The matched rows of the range-Doppler chain: at 4096 points with FP32
+// intermediates the squared powers, 203.5-204.2 against 204.6-205.5 us per
+// chain with the second stage's factors from LDS; with FP16 the latter
+// (183.8 against 186.4 us).
 template <int N>
-struct SmallRows {
-    static constexpr int variant = -1;     // index into Rows, or none
-    static constexpr long long below = 0;  // applies to batches below this
+struct RdRows {
+    static constexpr int v[2] = {Configs<N>::kRowMatched[0], Configs<N>::kRowMatched[1]};
 };
 template <>
-struct SmallRows<1024> {
-    static constexpr int variant = 4;
-    static constexpr long long below = 4 * 256;
+struct RdRows<4096> {
+    static constexpr int v[2] = {1, 9};
+};
+
+// Small batches: other shapes than the default up to `most` transforms.
+//   2048   up to 511, FP16: one transform per workgroup instead of two (64
+//          transforms, one flushed call, 7.3 against 8.1 us)
+//   8192   up to 2^25 points, FP32: three stages of 32 points per thread, 20.7
+//          against 21.8 us for 2^23 points, 94.8 / 96.0 for 2^25 (but 372 /
+//          355 for 2^27: memory-bound, the higher occupancy wins)
+//   16384  up to 2^23 points, FP32: the same, 10.2 / 11.4 us for 2^20 points,
+//          26.0 / 26.4-27.3 for 2^23 (2^25: 104.2 / 102.6)
+template <int N>
+struct SmallRows {
+    static constexpr int variant = -1;   // index into Rows, or none
+    static constexpr long long most = 0;
 };
 template <>
 struct SmallRows<2048> {
     static constexpr int variant = 4;
-    static constexpr long long below = 2 * 256;
+    static constexpr long long most = 511;
+};
+template <>
+struct SmallRows<8192> {
+    static constexpr int variant = 4;
+    static constexpr long long most = 4096;
+};
+template <>
+struct SmallRows<16384> {
+    static constexpr int variant = 4;
+    static constexpr long long most = 512;
 };
 
 // The column shape of a pass over `columns` columns in all (every problem of
@@ -453,8 +481,10 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
     const int half = (in_st | out_st) != 0;  // any FP16 storage involved
     const bool mf = epi == EPI_MATCHED || epi == EPI_MATCHED_Y;
     if (layout == LAYOUT_ROWS) {
-        int v = variant >= 0 ? variant : mf ? Configs<N>::kRowMatched[half] : Configs<N>::kRowDefault[half];
-        if (variant < 0 && !mf && epi == EPI_NONE && a.batch < SmallRows<N>::below) v = SmallRows<N>::variant;
+        int v = variant >= 0 ? variant
+                : mf         ? (a.rd_chain ? RdRows<N>::v[half] : Configs<N>::kRowMatched[half])
+                             : Configs<N>::kRowDefault[half];
+        if (variant < 0 && !mf && epi == EPI_NONE && a.batch <= SmallRows<N>::most) v = SmallRows<N>::variant;
         return with_variant(v, typename Configs<N>::Rows{}, f);
     }
     using Cols = typename Configs<N>::Cols;

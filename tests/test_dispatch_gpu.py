@@ -109,3 +109,20 @@ def test_images_by_shape(api, shape, inter):
     e = np.linalg.norm(img) / np.linalg.norm(ref)
     log(f"sar {n_az}x{n_rg} inter {inter}: rel {e:.2e}")
     assert e < TOL[inter]
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("n,batch", [(1024, 1), (1024, 1027), (2048, 511), (2048, 513), (4096, 1025), (8192, 1),
+                                     (8192, 4096), (8192, 4097), (16384, 17), (16384, 512), (16384, 513)])
+def test_rows_by_batch(api, storage, n, batch):
+    """Row shapes on both sides of their batch limits, odd batches and one."""
+    import torch
+
+    x = workloads.uniform_complex(batch, n, 5 + batch, "fp16" if storage else "fp32")
+    y = api.fft(to_dev(x), 1)
+    torch.cuda.synchronize()
+    pick = np.unique(np.r_[0, batch - 1, np.random.default_rng(batch).integers(0, batch, 10)])
+    got = widen(to_host(y[torch.from_numpy(pick).cuda()]))
+    e = rel_rows(got, oracle.fft(x[pick], 1)).max()
+    log(f"rows {n} x {batch} storage {storage}: rel {e:.2e}")
+    assert e < TOL[storage]
