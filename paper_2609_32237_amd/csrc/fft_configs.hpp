@@ -135,10 +135,8 @@ struct Configs<4096> {
                        // every factor from the per-stage tables
                        KCfg<4096, 16, 1, false, XCHG_FULL, 2, false, Radices<16, 16, 16>, false>,
                        KCfg<4096, 16, 1, false, XCHG_SPLIT, 2, false, Radices<16, 16, 16>>,
-                       // the complex exchange with streaming row stores, every
-                       // power of two read: 346.6-346.9 against 348.6-350.3 us
-                       // (32768 rows FP32, two read and two squared)
-                       KCfg<4096, 16, 1, false, XCHG_FULL, 4, false, Radices<16, 16, 16>, true>,
+                       // the complex exchange with streaming row stores
+                       KCfg<4096, 16, 1, false, XCHG_FULL, 1, false, Radices<16, 16, 16>, true>,
                        // the second stage's 240 factors from LDS (twiddle mode 3)
                        KCfg<4096, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16>>>;
     using Cols = KList<KCfg<4096, 32, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16>>,

@@ -109,14 +109,81 @@ __device__ __forceinline__ float2 twiddle_const(float2 a) {
 // small DFTs in registers: X[k] = sum_n x[n] W_R^{nk}, in place
 // --------------------------------------------------------------------------
 
-// Decimation in time, one radix-2 layer at a time: with h = 1, 2, 4, ..., R/2,
+template <int R, bool INV>
+struct Dft;
+
+template <bool INV>
+struct Dft<2, INV> {
+    __device__ __forceinline__ static void run(float2 *v) {
+        float2 a = v[0], b = v[1];
+        v[0] = cadd(a, b);
+        v[1] = csub(a, b);
+    }
+};
+
+template <bool INV>
+struct Dft<4, INV> {
+    __device__ __forceinline__ static void run(float2 *v) {
+        float2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
+        float2 t2 = cadd(v[1], v[3]), t3 = twiddle_const<4, 1, INV>(csub(v[1], v[3]));
+        v[0] = cadd(t0, t2);
+        v[2] = csub(t0, t2);
+        v[1] = cadd(t1, t3);
+        v[3] = csub(t1, t3);
+    }
+};
+
+// Composite R = R1 * R2: n = R2*n1 + n2, k = k1 + R1*k2.
+//   Y[n2][k1] = DFT_R1 over n1 of x[R2*n1 + n2], times W_R^{n2*k1};
+//   X[k1 + R1*k2] = DFT_R2 over n2 of Y[n2][k1].
+template <int R>
+struct DftSplit {
+    static constexpr int R1 = R == 8 ? 2 : R == 16 ? 4 : R == 32 ? 4 : 8;
+    static constexpr int R2 = R / R1;
+};
+
+template <int R, bool INV>
+struct Dft {
+    static_assert(R == 8 || R == 16 || R == 32 || R == 64, "unsupported radix");
+    __device__ __forceinline__ static void run(float2 *v) {
+        constexpr int R1 = DftSplit<R>::R1, R2 = DftSplit<R>::R2;
+        float2 y[R];
+        static_for<0, R2>([&](auto n2c) {
+            constexpr int n2 = decltype(n2c)::value;
+            float2 u[R1];
+            static_for<0, R1>([&](auto n1c) { u[n1c] = v[R2 * n1c + n2]; });
+            Dft<R1, INV>::run(u);
+            static_for<0, R1>([&](auto k1c) {
+                constexpr int k1 = decltype(k1c)::value;
+                y[n2 * R1 + k1] = twiddle_const<R, n2 * k1, INV>(u[k1]);
+            });
+        });
+        static_for<0, R1>([&](auto k1c) {
+            constexpr int k1 = decltype(k1c)::value;
+            float2 u[R2];
+            static_for<0, R2>([&](auto n2c) { u[n2c] = y[n2c * R1 + k1]; });
+            Dft<R2, INV>::run(u);
+            static_for<0, R2>([&](auto k2c) { v[k1 + R1 * k2c] = u[k2c]; });
+        });
+    }
+};
+
+// The same with a stage's twiddles, X[k] = sum_r x[r] w^r W_R^(r k), for
+// transforms of FP16 data: decimation in time, one radix-2 layer at a time,
+// with h = 1, 2, 4, ..., R/2,
 //   t = a + f b,  a <- t,  b <- 2 a - t   (f = w^(R/2h) W_2h^m, m < h)
-// on the pairs h apart of the bit-reversed inputs.  w is the stage's twiddle
-// base (input r carries w^r), so the twiddles ride in the butterflies' own
-// multiply-adds: t takes four of them and 2a - t (one rounding) two, 6 per
-// pair whether f is trivial or not, where a product and a sum took 10.  The
-// second half of each layer's factors is -i times the first half (a swap of
-// components), so a butterfly forms R/2 factors rather than R - 1.
+// on the pairs h apart of the bit-reversed inputs.  The twiddles ride in the
+// butterflies' own multiply-adds: t takes four of them and 2 a - t two, where
+// a product, a sum and a difference take eight.  The second half of each
+// layer's factors is -i times the first half (a swap of components), so a
+// butterfly forms R/2 factors rather than R - 1.
+//
+// 2 a - t carries t's rounding as well as its own (1.51e-7 against 1.48e-7
+// for the products and the radix-8 butterflies, 64 x 64 points) and is
+// infinite when t overflows though a - f b would not.  FP16 data hides the
+// first (2.07e-4 from its 11 bits either way) and rules the second out: its
+// sums (65504 N at most) stay far from FP32's range.  FP32 data does neither
+// and takes the products (tw_dft).
 constexpr int bitrev(int x, int bits) {
     int r = 0;
     for (int i = 0; i < bits; ++i) r |= ((x >> i) & 1) << (bits - 1 - i);
@@ -131,48 +198,11 @@ __device__ __forceinline__ void bfly(float2 &a, float2 &b, float fx, float fy) {
     a = make_float2(tx, ty);
 }
 
-// the same for f = W_L^m (forward; its conjugate for the inverse), L <= 64:
-// no multiply where f is a power of -i
-template <int L, int M, bool INV>
-__device__ __forceinline__ void bfly_const(float2 &a, float2 &b) {
-    constexpr int m = M % L;
-    if constexpr ((4 * m) % L == 0) {
-        const float2 r = twiddle_const<L, m, INV>(b);
-        const float2 s = a;
-        a = cadd(s, r);
-        b = csub(s, r);
-    } else {
-        static_assert(64 % L == 0, "constant factors cover lengths dividing 64");
-        constexpr float c = cos64(m * (64 / L)), sn = INV ? sin64(m * (64 / L)) : -sin64(m * (64 / L));
-        bfly(a, b, c, sn);
-    }
-}
-
-// X[k] = sum_r x[r] W_R^(r k), in place (natural order in and out)
+// pw[i] = w^(2^i) (forward; conjugated here for the inverse)
 template <int R, bool INV>
-struct Dft {
-    static_assert((R & (R - 1)) == 0 && R >= 2 && R <= 64, "unsupported radix");
+struct DftLayers {
     template <int H>
-    __device__ __forceinline__ static void layer(float2 (&y)[R]) {
-        static_for<0, H>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            static_for<0, R / (2 * H)>([&](auto gc) {
-                constexpr int i = 2 * H * decltype(gc)::value + m;
-                bfly_const<2 * H, m, INV>(y[i], y[i + H]);
-            });
-        });
-        if constexpr (2 * H < R) layer<2 * H>(y);
-    }
-    __device__ __forceinline__ static void run(float2 *v) {
-        float2 y[R];
-        static_for<0, R>([&](auto rc) { y[bitrev(rc, ilog2(R))] = v[rc]; });
-        layer<1>(y);
-        static_for<0, R>([&](auto rc) { v[rc] = y[rc]; });
-    }
-    // X[k] = sum_r x[r] w^r W_R^(r k); pw[i] = w^(2^i) (forward; conjugated
-    // here for the inverse)
-    template <int H>
-    __device__ __forceinline__ static void layer_tw(float2 (&y)[R], const float2 *pw) {
+    __device__ __forceinline__ static void layer(float2 (&y)[R], const float2 *pw) {
         const float2 w = pw[ilog2(R) - 1 - ilog2(H)];  // w^(R / 2H)
         static_for<0, (H > 1 ? H / 2 : 1)>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
@@ -184,12 +214,12 @@ struct Dft {
                 if constexpr (H > 1) bfly(y[i2], y[i2 + H], f.y, INV ? f.x : -f.x);
             });
         });
-        if constexpr (2 * H < R) layer_tw<2 * H>(y, pw);
+        if constexpr (2 * H < R) layer<2 * H>(y, pw);
     }
-    __device__ __forceinline__ static void run_tw(float2 *v, const float2 *pw) {
+    __device__ __forceinline__ static void run(float2 *v, const float2 *pw) {
         float2 y[R];
         static_for<0, R>([&](auto rc) { y[bitrev(rc, ilog2(R))] = v[rc]; });
-        layer_tw<1>(y, pw);
+        layer<1>(y, pw);
         static_for<0, R>([&](auto rc) { v[rc] = y[rc]; });
     }
 };

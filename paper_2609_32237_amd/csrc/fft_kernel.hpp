@@ -28,19 +28,15 @@
 //          exchange is a register/lane transpose made with cross-lane
 //          instructions (fft_lane.hpp).
 //   TWMODE 0: every inter-stage twiddle read from the table;
-//          1: one table read per base-4 digit of the radix, the other powers
-//          of two as squares, multiplied in the butterflies' layers
-//          (fewest loads and fewest FP32 operations);
+//          1: one table read per base-4 digit of the radix, the rest formed
+//          by complex products, or for FP16 data by squares multiplied in the
+//          butterflies' layers (fewest loads);
 //          2: every factor read from the stage's own table, laid out so that
 //          consecutive lanes read consecutive entries (no products: fewer
 //          FP32 operations than 1, more loads, each one coalesced);
 //          3: stages whose own table is small (at most kLdsTwEntries
 //          factors) read every factor from a copy of that table in LDS, which
-//          the workgroup fills once; the other stages work as in mode 1;
-//          4: as mode 1, but every power of two is read, from the stage's own
-//          table (consecutive lanes, consecutive entries): fewest operations
-//          and least rounding error (4096 points 1.46e-7 against 1.50e-7),
-//          two more reads per butterfly.
+//          the workgroup fills once; the other stages work as in mode 1.
 //   PERSIST the workgroup loops over its share of the batch and loads the
 //          next transform into a second register array while it computes the
 //          current one (the second-array idea of Section VI, used here to
@@ -201,7 +197,7 @@ struct TwRegs {
     // butterflies per thread, 62 at radix 32, either of which spills.  Those
     // stages read each butterfly's factors just before applying them instead.
     static constexpr bool LATE = MODE == 2 && (B > 1 || R >= 32);
-    static constexpr int LOADS = NS == 1 || LATE || MODE == 3 ? 0 : (MODE == 1 ? num_digits4(R) : MODE == 4 ? ilog2(R) : R - 1);
+    static constexpr int LOADS = NS == 1 || LATE || MODE == 3 ? 0 : (MODE == 1 ? num_digits4(R) : R - 1);
     float2 w[B][LOADS > 0 ? LOADS : 1];
 };
 
@@ -225,14 +221,6 @@ __device__ __forceinline__ void tw_issue(TwRegs<K, NS, R> &tr, int t, const floa
                 static_for<1, R>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
                     tr.w[q][r - 1] = tw[OFF + (r - 1) * NS + k];
-                });
-            } else if constexpr (TwRegs<K, NS, R>::MODE == 4) {
-                // W^(k 2^i) is row 2^i - 1 of the stage's table
-                static_assert(R <= 32, "stage tables reach radix 32");
-                constexpr long long OFF = stage_table_offset(K::N, NS, R);
-                static_for<0, ilog2(R)>([&](auto ic) {
-                    constexpr int i = decltype(ic)::value;
-                    tr.w[q][i] = tw[OFF + ((1 << i) - 1) * NS + k];
                 });
             } else {
                 static_for<0, TwRegs<K, NS, R>::LOADS>([&](auto ic) {
@@ -259,31 +247,74 @@ __device__ __forceinline__ float2 unit_square(float2 w) {
     return make_float2(re, -t * w.x);
 }
 
-// The stage's DFT with its twiddles, u[r] W^(k r) (conjugate for the inverse),
-// r = 0..R-1.  With the digit-base reads (TWMODE 1) the layers of the
-// decimation in time need only the powers W^(k 2^i): the even ones are read,
-// the odd ones their squares (reading all of them was 2-6% slower on the
-// issue-bound kernels: 16384 FP16 rows 425-436 against 437-447 us; mode 4 does
-// so where memory is the bound).  The other modes multiply first.
-// Against multiplying every input by its own factor (formed by up to three
-// products) and a radix-4 butterfly, VALU instructions per point fall from
-// 44 to 37 at 4096 points, at 2% less rounding error (relative to FP64,
-// 4096 points: 1.50e-7 against 1.53e-7).
+// Multiply u[r] by w[r] = W^{k r} (its conjugate for the inverse), r = 1..R-1.
+// With the digit-base reads (TWMODE 1), r = low + 16 h with low < 16:
+// w[low] is the product of its two base-4 digit parts and w[r] = w[low] *
+// w[16 h].  Each factor is applied as soon as it is formed, so only the digit
+// bases and one partial product are live at a time rather than all R - 1
+// factors (31 complex values at radix 32, which would spill).  The products
+// are the same, in the same order, as forming every factor first.
 template <class K, int NS, int R, int q, bool INV>
-__device__ __forceinline__ void tw_dft(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
-    if constexpr (TwRegs<K, NS, R>::MODE == 4) {
-        Dft<R, INV>::run_tw(u, tr.w[q]);
-    } else if constexpr (TwRegs<K, NS, R>::MODE != 1) {
-        static_for<1, R>([&](auto rc) { u[rc] = INV ? cmulc(u[rc], tr.w[q][rc - 1]) : cmul(u[rc], tr.w[q][rc - 1]); });
-        Dft<R, INV>::run(u);
+__device__ __forceinline__ void tw_apply(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
+    auto mul = [](float2 a, float2 w) { return INV ? cmulc(a, w) : cmul(a, w); };
+    if constexpr (TwRegs<K, NS, R>::MODE != 1) {
+        static_for<1, R>([&](auto rc) { u[rc] = mul(u[rc], tr.w[q][rc - 1]); });
     } else {
+        constexpr int D = TwRegs<K, NS, R>::LOADS;
+        float2 b[D][3];  // b[i][d - 1] = W^{k d 4^i}
+        static_for<0, D>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            constexpr int base = pow4(i);
+            b[i][0] = tr.w[q][i];
+            if constexpr (2 * base < R) b[i][1] = cmul(b[i][0], b[i][0]);
+            if constexpr (3 * base < R) b[i][2] = cmul(b[i][1], b[i][0]);
+        });
+        constexpr int LOW = R < 16 ? R : 16;
+        static_for<0, LOW>([&](auto lc) {
+            constexpr int low = decltype(lc)::value;
+            constexpr int d0 = low % 4, d1 = low / 4;
+            float2 wl = make_float2(1.0f, 0.0f);
+            if constexpr (d0 != 0 && d1 != 0) wl = cmul(b[0][d0 - 1], b[1][d1 - 1]);
+            if constexpr (d0 != 0 && d1 == 0) wl = b[0][d0 - 1];
+            if constexpr (d0 == 0 && d1 != 0) wl = b[1][d1 - 1];
+            if constexpr (low != 0) u[low] = mul(u[low], wl);
+            static_for<1, (R + 15) / 16>([&](auto hc) {
+                constexpr int r = low + 16 * decltype(hc)::value;
+                if constexpr (r < R) {
+                    const float2 bh = b[2][decltype(hc)::value - 1];
+                    if constexpr (low != 0) {
+                        u[r] = mul(u[r], cmul(wl, bh));
+                    } else {
+                        u[r] = mul(u[r], bh);
+                    }
+                }
+            });
+        });
+    }
+}
+
+// The stage's DFT with its twiddles.  LAYERED (FP16 data): with the digit-base
+// reads the layers need only the powers W^(k 2^i): the even ones are read, the
+// odd ones their squares (reading all of them was 2-6% slower: 16384 FP16 rows
+// 425-436 against 437-447 us).  Per point of a 16384-point FP16 row 45 VALU
+// instructions against 52 with the products.  FP32 data multiplies first: its
+// overflow and rounding are DftLayers' concern, and keeping both outputs of
+// the layers' butterflies as multiply-adds of the inputs, which has neither
+// fault, was slower (4096 x 4096 range-Doppler chain 206.9 against 200.3 us,
+// SAR 141.9 / 139.9, 4096 x 4096 columns 77.2 / 76.4).
+template <class K, int NS, int R, int q, bool INV, bool LAYERED>
+__device__ __forceinline__ void tw_dft(const TwRegs<K, NS, R> &tr, float2 (&u)[R]) {
+    if constexpr (LAYERED && TwRegs<K, NS, R>::MODE == 1) {
         float2 pw[ilog2(R)];
         static_for<0, ilog2(R)>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             // W^(k 2^(i-1)) turns by at most 2 pi 2^(i-1) / R
             pw[i] = i % 2 == 0 ? tr.w[q][i / 2] : unit_square<((4 << i) <= R)>(tr.w[q][i / 2]);
         });
-        Dft<R, INV>::run_tw(u, pw);
+        DftLayers<R, INV>::run(u, pw);
+    } else {
+        tw_apply<K, NS, R, q, INV>(tr, u);
+        Dft<R, INV>::run(u);
     }
 }
 
@@ -369,7 +400,7 @@ struct FirstOf {
 // One radix-R stage on sub-transforms of length NS: twiddle, butterfly in
 // registers; then (unless last) request the next stage's twiddles and
 // exchange through LDS.
-template <class K, bool INV, bool FIRST_X, int NS, int R, int... Rest>
+template <class K, bool INV, bool LAYERED, bool FIRST_X, int NS, int R, int... Rest>
 __device__ __forceinline__ void run_stages(float2 (&v)[K::P], int t, int c, const float2 *__restrict__ tw,
                                            float *lds, const TwRegs<K, NS, R> &cur) {
     constexpr int P = K::P, B = P / R;
@@ -400,7 +431,7 @@ __device__ __forceinline__ void run_stages(float2 (&v)[K::P], int t, int c, cons
             });
             Dft<R, INV>::run(u);
         } else if constexpr (NS > 1) {
-            tw_dft<K, NS, R, q, INV>(cur, u);
+            tw_dft<K, NS, R, q, INV, LAYERED>(cur, u);
         } else {
             Dft<R, INV>::run(u);
         }
@@ -411,7 +442,7 @@ __device__ __forceinline__ void run_stages(float2 (&v)[K::P], int t, int c, cons
         TwRegs<K, NS2, R2> nxt;
         tw_issue<K, NS2, R2>(nxt, t, tw);  // in flight during the exchange
         exchange<K, NS, R, FIRST_X>(v, t, c, lds);
-        run_stages<K, INV, false, NS2, Rest...>(v, t, c, tw, lds, nxt);
+        run_stages<K, INV, LAYERED, false, NS2, Rest...>(v, t, c, tw, lds, nxt);
     }
 }
 
@@ -453,11 +484,11 @@ struct LdsTwFillOf<K, Radices<Rs...>> {
     using type = LdsTwFill<K, 1, Rs...>;
 };
 
-template <class K, bool INV, bool FIRST_X, int R1, int... Rs>
+template <class K, bool INV, bool LAYERED, bool FIRST_X, int R1, int... Rs>
 __device__ __forceinline__ void run_fft(Radices<R1, Rs...>, float2 (&v)[K::P], int t, int c,
                                         const float2 *__restrict__ tw, float *lds) {
     TwRegs<K, 1, R1> none;  // the first stage has no twiddles
-    run_stages<K, INV, FIRST_X, 1, R1, Rs...>(v, t, c, tw, lds, none);
+    run_stages<K, INV, LAYERED, FIRST_X, 1, R1, Rs...>(v, t, c, tw, lds, none);
 }
 
 }  // namespace mi355fft
@@ -847,7 +878,7 @@ __device__ __forceinline__ void wait_for_reference(unsigned long long *flag, uns
 // kernel may skip its leading barrier).
 // t and c are the caller's lane coordinates; the fused inverse launders them
 // in place (below), so the caller keeps one copy of them, not two.
-template <class K, bool INV, int EPI, bool FIRST_X>
+template <class K, bool INV, int EPI, bool LAYERED, bool FIRST_X>
 __device__ __forceinline__ void transform(float2 (&v)[K::P], int &t, int &c, const float2 *__restrict__ tw,
                                           const float2 *__restrict__ spec, float scale, float *lds,
                                           int spec_off = 0, int spec_shift = 0,
@@ -855,9 +886,9 @@ __device__ __forceinline__ void transform(float2 (&v)[K::P], int &t, int &c, con
     constexpr bool MF = EPI == EPI_MATCHED || EPI == EPI_MATCHED_Y;
     if constexpr (K::XCHG == XCHG_LANE) {
         static_assert(EPI == EPI_NONE, "the cross-lane kernels run plain transforms");
-        lane_fft_1024<K, INV>(v, t, tw);
+        lane_fft_1024<K, INV, LAYERED>(v, t, tw);
     } else {
-        run_fft<K, INV, FIRST_X>(typename K::Rad{}, v, t, c, tw, lds);
+        run_fft<K, INV, LAYERED, FIRST_X>(typename K::Rad{}, v, t, c, tw, lds);
     }
     if constexpr (MF) {
         // X[k] * conj(H[k]), k = t + T*i, then the inverse transform.
@@ -890,7 +921,7 @@ __device__ __forceinline__ void transform(float2 (&v)[K::P], int &t, int &c, con
         // uses the laundered copies.
         const float2 *tw2 = tw;
         asm volatile("" : "+s"(tw2), "+v"(t), "+v"(c));
-        run_fft<K, !INV, false>(typename K::Rad{}, v, t, c, tw2, lds);
+        run_fft<K, !INV, false, false>(typename K::Rad{}, v, t, c, tw2, lds);
     }
     if constexpr (EPI == EPI_SCALE) {
         static_for<0, K::P>([&](auto ic) {
@@ -929,7 +960,7 @@ __device__ __forceinline__ void reference_rows(float2 (&v)[K::P], long long blk,
     static_for<0, K::P>([&](auto ic) { v[ic] = src[t + K::T * decltype(ic)::value]; });
     if constexpr (K::TWL > 0) twl.store(lds);
     int tt = t, cc = c;
-    transform<K, false, EPI_NONE, true>(v, tt, cc, tw, nullptr, second ? a.ref_scale[1] : a.ref_scale[0], lds);
+    transform<K, false, EPI_NONE, false, true>(v, tt, cc, tw, nullptr, second ? a.ref_scale[1] : a.ref_scale[0], lds);
     if (mine) {
         float2 *dst = second ? a.ref_out[1] : a.ref_out[0];
         static_for<0, K::P>([&](auto ic) { dst[t + K::T * decltype(ic)::value] = v[ic]; });
@@ -974,6 +1005,9 @@ void fft_kernel(const void *__restrict__ in, void *__restrict__ out,
     // one: 2.5-2.8% on the FP16 row transforms, while the memory-bound FP32
     // kernels lose up to 10% with it.
     constexpr bool PRIO = IN_ST == 1 && OUT_ST == 1;
+    // the form of the twiddled butterflies (tw_dft): by layers for FP16 data;
+    // a matched pass's inverse, of products with an FP32 spectrum, never
+    constexpr bool LAYERED = IN_ST == 1;
     if (blockIdx.y | blockIdx.z) {  // independent problems along the grid's second and third axes
         const long long in_off = (long long)blockIdx.y * a.outer_in_dist + (long long)blockIdx.z * a.outer2_dist;
         const long long out_off = (long long)blockIdx.y * a.outer_out_dist + (long long)blockIdx.z * a.outer2_dist;
@@ -1024,16 +1058,16 @@ void fft_kernel(const void *__restrict__ in, void *__restrict__ out,
         }
         if constexpr (EPI == EPI_RCMC) {
             rcmc_load<K, IN_ST>(v, in, blk, c, t, valid, a, spec, lds);
-            transform<K, INV, EPI_NONE, true>(v, t, c, tw, spec, a.scale, lds);
+            transform<K, INV, EPI_NONE, LAYERED, true>(v, t, c, tw, spec, a.scale, lds);
         } else {
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(3);
             load_points<K, IN_ST>(v, in, blk, c, t, valid, a);
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
             if constexpr (K::TWL > 0) twl.store(lds);
             if constexpr (EPI == EPI_MATCHED_Y) {
-                transform<K, INV, EPI, true>(v, t, c, tw, spec, a.scale, lds, (int)blockIdx.y, a.spec_shift);
+                transform<K, INV, EPI, LAYERED, true>(v, t, c, tw, spec, a.scale, lds, (int)blockIdx.y, a.spec_shift);
             } else {
-                transform<K, INV, EPI, true>(v, t, c, tw, spec, a.scale, lds, 0, 0, a.ref_flag, a.ref_epoch);
+                transform<K, INV, EPI, LAYERED, true>(v, t, c, tw, spec, a.scale, lds, 0, 0, a.ref_flag, a.ref_epoch);
             }
         }
         if constexpr (EPI == EPI_TWIDDLE || EPI == EPI_TWIDDLE_Y || EPI == EPI_MATCHED_Y) {
@@ -1112,7 +1146,7 @@ void fft_kernel(const void *__restrict__ in, void *__restrict__ out,
             const bool nvalid = nblk2 * K::C + c < a.batch;
             float2 nv[K::P];
             if (nblk2 < nblk) load_points<K, IN_ST>(nv, in, nblk2, c, t, nvalid, a);  // uniform
-            transform<K, INV, EPI, false>(v, t, c, tw, spec, a.scale, lds);
+            transform<K, INV, EPI, LAYERED, false>(v, t, c, tw, spec, a.scale, lds);
             if (valid) store_points<K, OUT_ST, NT>(v, out, blk, c, t, a);
             static_for<0, K::P>([&](auto ic) { v[ic] = nv[ic]; });
             valid = nvalid;

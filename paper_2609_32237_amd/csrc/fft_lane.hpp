@@ -91,7 +91,7 @@ __device__ __forceinline__ void lane_transpose_bit(float2 (&v)[P], int lane) {
 
 // The 1024-point transform of one wave (layout above), forward or inverse.
 // tw is the 1024-entry twiddle table; K supplies the twiddle mode.
-template <class K, bool INV>
+template <class K, bool INV, bool LAYERED>
 __device__ __forceinline__ void lane_fft_1024(float2 (&v)[16], int lane, const float2 *__restrict__ tw) {
     static_assert(K::N == 1024 && K::P == 16 && K::T == 64, "one wave holds one 1024-point transform");
     // stage 2's twiddles W_256^(k r), k = L >> 2: requested before stage 1
@@ -110,7 +110,7 @@ __device__ __forceinline__ void lane_fft_1024(float2 (&v)[16], int lane, const f
     TwRegs<K, 256, 4> tw3;
     tw_issue<K, 256, 4>(tw3, base, tw);
     // stage 2: radix 16 on sub-transforms of length 16
-    tw_dft<K, 16, 16, 0, INV>(tw2, v);
+    tw_dft<K, 16, 16, 0, INV, LAYERED>(tw2, v);
     // exchange: register bits 0..1 <-> lane bits 0..1
     lane_transpose_bit<0, 0>(v, lane);
     lane_transpose_bit<1, 1>(v, lane);
@@ -119,7 +119,7 @@ __device__ __forceinline__ void lane_fft_1024(float2 (&v)[16], int lane, const f
         constexpr int q = decltype(qc)::value;
         float2 u[4];
         static_for<0, 4>([&](auto rc) { u[rc] = v[4 * q + rc]; });
-        tw_dft<K, 256, 4, q, INV>(tw3, u);
+        tw_dft<K, 256, 4, q, INV, LAYERED>(tw3, u);
         static_for<0, 4>([&](auto rc) { v[4 * q + rc] = u[rc]; });
     });
 }
