@@ -84,7 +84,13 @@ struct Configs<1024> {
     // two stages, one exchange; 8 or 16 columns (64-byte pieces or whole lines in FP32)
     using Cols = KList<KCfg<1024, 32, 8, true, XCHG_SPLIT, 1, false, Radices<32, 32>>,
                        KCfg<1024, 32, 16, true, XCHG_SPLIT, 1, false, Radices<32, 32>>,
-                       KCfg<1024, 16, 8, true, XCHG_FULL, 0, false, Radices<16, 16, 4>>>;
+                       KCfg<1024, 16, 8, true, XCHG_FULL, 0, false, Radices<16, 16, 4>>,
+                       // the second stage's 992 factors from LDS: FP32 SAR images, in whose
+                       // two transforms a computed factor's rounding counts twice (error
+                       // against FP64 over 1024 columns 3.77e-7, with computed factors
+                       // 3.98e-7; 24.6 / 24.0 us)
+                       KCfg<1024, 32, 8, true, XCHG_SPLIT, 3, false, Radices<32, 32>>,
+                       KCfg<1024, 32, 16, true, XCHG_SPLIT, 3, false, Radices<32, 32>>>;
     // 8 range bins per strip: 229 against 256 us for 16 (which held one
     // Doppler bin per thread, too few for the column gather) on a 1024 x 16384
     // range-Doppler chain
@@ -141,7 +147,9 @@ struct Configs<4096> {
                        KCfg<4096, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16>>>;
     using Cols = KList<KCfg<4096, 32, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16>>,
                        KCfg<4096, 32, 4, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16>>,
-                       KCfg<4096, 16, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16>>,
+                       // (the second stage's factors from LDS: error against FP64
+                       // 1.35e-7, with computed factors 1.51e-7)
+                       KCfg<4096, 16, 4, true, XCHG_SPLIT, 3, false, Radices<16, 16, 16>>,
                        KCfg<4096, 32, 8, true, XCHG_SPLIT, 1, false, Radices<16, 16, 16>>,
                        KCfg<4096, 32, 8, true, XCHG_SPLIT, 2, false, Radices<16, 16, 16>>,
                        // two radix-64 stages, 64 points per thread: one exchange per
@@ -185,11 +193,16 @@ struct Configs<8192> {
                        KCfg<8192, 32, 1, false, XCHG_SPLIT, 2, false, Radices<32, 16, 16>>,
                        KCfg<8192, 16, 1, false, XCHG_SPLIT, 2, false, Radices<16, 16, 16, 2>>,
                        // the second stage's 240 factors from LDS (twiddle mode 3)
-                       KCfg<8192, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 2>>>;
-    // three stages; 4 columns hold a CU (64 or 32 points per thread), 2 columns half
-    using Cols = KList<KCfg<8192, 64, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
-                       KCfg<8192, 32, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
-                       KCfg<8192, 32, 2, true, XCHG_SPLIT, 1, false, Radices<16, 16, 32>>,
+                       KCfg<8192, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 2>>,
+                       // three stages with the second one's 480 factors from LDS
+                       KCfg<8192, 32, 1, false, XCHG_SPLIT, 3, false, Radices<32, 16, 16>>>;
+    // three stages, the second one's 240 factors from LDS (error against FP64
+    // 1.43e-7 in FP32, with squared powers in the layers 1.61e-7; 4096 columns
+    // in place 219 / 227 us); 4 columns hold a CU (64 or 32 points per
+    // thread), 2 columns half
+    using Cols = KList<KCfg<8192, 64, 4, true, XCHG_SPLIT, 3, false, Radices<16, 16, 32>>,
+                       KCfg<8192, 32, 4, true, XCHG_SPLIT, 3, false, Radices<16, 16, 32>>,
+                       KCfg<8192, 32, 2, true, XCHG_SPLIT, 3, false, Radices<16, 16, 32>>,
                        KCfg<8192, 32, 2, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16, 2>>>;
     using Rcmc = KList<KCfg<8192, 32, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 2>>,
                        KCfg<8192, 16, 2, false, XCHG_SPLIT, 1, false, Radices<16, 16, 16, 2>>>;
@@ -213,7 +226,9 @@ struct Configs<16384> {
                        KCfg<16384, 32, 1, false, XCHG_SPLIT, 1, false, Radices<32, 16, 32>>,
                        KCfg<16384, 32, 1, false, XCHG_SPLIT, 2, false, Radices<32, 16, 32>>,
                        // the second stage's 240 factors from LDS (twiddle mode 3)
-                       KCfg<16384, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 4>>>;
+                       KCfg<16384, 16, 1, false, XCHG_SPLIT, 3, false, Radices<16, 16, 16, 4>>,
+                       // three stages with the second one's 480 factors from LDS
+                       KCfg<16384, 32, 1, false, XCHG_SPLIT, 3, false, Radices<32, 16, 32>>>;
     using Cols = KList<KCfg<16384, 32, 2, true, XCHG_SPLIT, 1, false, Radices<32, 16, 32>>,
                        KCfg<16384, 32, 1, true, XCHG_SPLIT, 1, false, Radices<32, 16, 32>>,
                        KCfg<16384, 32, 1, true, XCHG_SPLIT, 0, false, Radices<16, 16, 16, 4>>>;
@@ -246,34 +261,25 @@ struct RdRows<4096> {
     static constexpr int v[2] = {1, 9};
 };
 
-// Small batches: other shapes than the default up to `most` transforms.
-//   2048   up to 511, FP16: one transform per workgroup instead of two (64
+// The row shape of a plain transform (index into Rows) by its storage and
+// batch.  Times in us, back to back on inputs that no cache holds.
+//   2048   FP16, up to 511: one transform per workgroup instead of two (64
 //          transforms, one flushed call, 7.3 against 8.1 us)
-//   8192   up to 2^25 points, FP32: three stages of 32 points per thread, 20.7
-//          against 21.8 us for 2^23 points, 94.8 / 96.0 for 2^25 (but 372 /
-//          355 for 2^27: memory-bound, the higher occupancy wins)
-//   16384  up to 2^23 points, FP32: the same, 10.2 / 11.4 us for 2^20 points,
-//          26.0 / 26.4-27.3 for 2^23 (2^25: 104.2 / 102.6)
+//   8192   FP32, up to 2^25 points: three stages of 32 points per thread, 26.1
+//          against 28.5 for 1024 transforms, 93.5 / 96.1 for 4096 (7.1 / 7.0
+//          for one); beyond, memory-bound, the higher occupancy wins (8192
+//          transforms 182.3 / 183.4).  Both shapes read the second stage's
+//          factors from LDS: error against FP64 1.40e-7 and 1.41e-7, where
+//          squared powers gave 1.59e-7.
+//   16384  FP32, up to 2^23 points: the same (10.0 against 11.1 for one
+//          transform; error 1.49e-7 and 1.50e-7, with squared powers 1.69e-7)
 template <int N>
-struct SmallRows {
-    static constexpr int variant = -1;   // index into Rows, or none
-    static constexpr long long most = 0;
-};
-template <>
-struct SmallRows<2048> {
-    static constexpr int variant = 4;
-    static constexpr long long most = 511;
-};
-template <>
-struct SmallRows<8192> {
-    static constexpr int variant = 4;
-    static constexpr long long most = 4096;
-};
-template <>
-struct SmallRows<16384> {
-    static constexpr int variant = 4;
-    static constexpr long long most = 512;
-};
+constexpr int row_shape(int half, long long batch) {
+    if (N == 2048 && half && batch <= 511) return 4;
+    if (N == 8192 && !half && batch <= 4096) return 8;
+    if (N == 16384 && !half && batch <= 512) return 7;
+    return Configs<N>::kRowDefault[half];
+}
 
 // The column shape of a pass over `columns` columns in all (every problem of
 // the grid counted), by what the pass does:
@@ -309,7 +315,10 @@ enum { COLS_PLAIN, COLS_TWIDDLED, COLS_SCALED, COLS_MATCHED };
 template <int N>
 constexpr int column_shape(int use, int half, long long columns) {
     if (N == 256 || N == 512) return columns >= 32768 ? 1 : 0;
-    if (N == 1024) return columns >= (use == COLS_MATCHED ? 16384 : 8192) ? 1 : 0;
+    if (N == 1024) {
+        if (use != COLS_MATCHED) return columns >= 8192 ? 1 : 0;
+        return (half ? 0 : 3) + (columns >= 16384 ? 1 : 0);
+    }
     if (N == 2048) {
         if (columns < 2048 || (use == COLS_SCALED && columns < 4096)) return 0;
         if (columns < 4096 || use == COLS_TWIDDLED) return 1;
@@ -479,10 +488,9 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
     const int half = (in_st | out_st) != 0;  // any FP16 storage involved
     const bool mf = epi == EPI_MATCHED || epi == EPI_MATCHED_Y;
     if (layout == LAYOUT_ROWS) {
-        int v = variant >= 0 ? variant
-                : mf         ? (a.rd_chain ? RdRows<N>::v[half] : Configs<N>::kRowMatched[half])
-                             : Configs<N>::kRowDefault[half];
-        if (variant < 0 && !mf && epi == EPI_NONE && a.batch <= SmallRows<N>::most) v = SmallRows<N>::variant;
+        const int v = variant >= 0 ? variant
+                      : mf         ? (a.rd_chain ? RdRows<N>::v[half] : Configs<N>::kRowMatched[half])
+                                   : row_shape<N>(half, a.batch);
         return with_variant(v, typename Configs<N>::Rows{}, f);
     }
     using Cols = typename Configs<N>::Cols;
