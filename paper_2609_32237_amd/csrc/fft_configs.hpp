@@ -97,10 +97,10 @@ struct Configs<1024> {
     using Rcmc = KList<KCfg<1024, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>,
                        KCfg<1024, 16, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>>;
     using RowsHalf = KList<KCfg<1024, 16, 4, false, XCHG_HALF, 1, false, Radices<16, 16, 4>>>;
-    // one transform, one wave, per workgroup (no barrier waits): FP16 47.8
-    // against 51.4 us for 2^25 points, FP32 89.0 / 89.2; matched, SAR 1024 x
-    // 1024 21.0 / 21.9 us, 4096 x 1024 50.4 / 51.2
-    static constexpr int kRowDefault[2] = {4, 4};
+    // (plain rows go by their batch, row_shape)
+    // matched: one transform, one wave, per workgroup, SAR 1024 x 1024 21.0 /
+    // 21.9 us, 4096 x 1024 50.4 / 51.2
+    static constexpr int kRowDefault[2] = {1, 0};
     static constexpr int kRowMatched[2] = {4, 4};
 };
 template <>
@@ -263,6 +263,12 @@ struct RdRows<4096> {
 
 // The row shape of a plain transform (index into Rows) by its storage and
 // batch.  Times in us, back to back on inputs that no cache holds.
+//   1024   one wave, one transform per workgroup (no barrier waits) against
+//          four of each: FP32 6.5 / 7.4 for 1500 transforms, 8.7 / 8.9 for
+//          2500, but 12.8 / 11.8 for 4096, 25.9 / 25.4 for 8192, 57.9 / 56.6 for
+//          20000 (87.0 / 89.2 for 32768, 351 / 347 for 131072); FP16 5.7 / 6.2
+//          for 2048, 7.9 / 8.2 for 4096, 11.4 / 9.5 for 5000, 15.8 / 14.1 for
+//          8192, 21.9 / 22.5 for 12288, 48.4 / 50.4 for 32768
 //   2048   FP16, up to 511: one transform per workgroup instead of two (64
 //          transforms, one flushed call, 7.3 against 8.1 us)
 //   8192   FP32, up to 2^25 points: three stages of 32 points per thread, 26.1
@@ -275,6 +281,7 @@ struct RdRows<4096> {
 //          transform; error 1.49e-7 and 1.50e-7, with squared powers 1.69e-7)
 template <int N>
 constexpr int row_shape(int half, long long batch) {
+    if (N == 1024) return half ? (batch <= 4096 || batch >= 12288 ? 4 : 0) : (batch <= 3072 ? 4 : 1);
     if (N == 2048 && half && batch <= 511) return 4;
     if (N == 8192 && !half && batch <= 4096) return 8;
     if (N == 16384 && !half && batch <= 512) return 7;

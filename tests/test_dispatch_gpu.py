@@ -126,3 +126,11 @@ def test_rows_by_batch(api, storage, n, batch):
     e = rel_rows(got, oracle.fft(x[pick], 1)).max()
     log(f"rows {n} x {batch} storage {storage}: rel {e:.2e}")
     assert e < TOL[storage]
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("n,batch", [(1024, 3072), (1024, 3073), (1024, 4096), (1024, 4097), (1024, 12287),
+                                     (1024, 12289)])
+def test_rows_by_batch_limits(api, storage, n, batch):
+    """Both sides of the remaining batch limits of the row shapes."""
+    test_rows_by_batch(api, storage, n, batch)
