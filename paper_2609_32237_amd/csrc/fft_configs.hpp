@@ -271,6 +271,9 @@ struct RdRows<4096> {
 //          8192, 21.9 / 22.5 for 12288, 48.4 / 50.4 for 32768
 //   2048   FP16, up to 511: one transform per workgroup instead of two (64
 //          transforms, one flushed call, 7.3 against 8.1 us)
+//   4096   FP16, up to 2048: every factor computed, 5.3 against 5.6 for 300
+//          transforms (filling the LDS table is not repaid), 6.2 / 6.6 for 512,
+//          8.2 / 8.5 for 800, level from 1024 to 2048, 29.9 / 27.8 for 4096
 //   8192   FP32, up to 2^25 points: three stages of 32 points per thread, 26.1
 //          against 28.5 for 1024 transforms, 93.5 / 96.1 for 4096 (7.1 / 7.0
 //          for one); beyond, memory-bound, the higher occupancy wins (8192
@@ -283,6 +286,7 @@ template <int N>
 constexpr int row_shape(int half, long long batch) {
     if (N == 1024) return half ? (batch <= 4096 || batch >= 12288 ? 4 : 0) : (batch <= 3072 ? 4 : 1);
     if (N == 2048 && half && batch <= 511) return 4;
+    if (N == 4096 && half && batch <= 2048) return 1;
     if (N == 8192 && !half && batch <= 4096) return 8;
     if (N == 16384 && !half && batch <= 512) return 7;
     return Configs<N>::kRowDefault[half];
