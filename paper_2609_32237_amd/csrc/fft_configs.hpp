@@ -280,15 +280,17 @@ struct RdRows<4096> {
 //          transforms 182.3 / 183.4).  Both shapes read the second stage's
 //          factors from LDS: error against FP64 1.40e-7 and 1.41e-7, where
 //          squared powers gave 1.59e-7.
-//   16384  FP32, up to 2^23 points: the same (10.0 against 11.1 for one
-//          transform; error 1.49e-7 and 1.50e-7, with squared powers 1.69e-7)
+//   16384  FP32, up to 127, half of the CUs: the same (10.0 against 11.1 for
+//          one transform, 12.7 / 13.3 for 100, but 14.3 / 14.1 for 128, 20.6 /
+//          18.9 for 256, 31.0 / 29.7 for 512, 59.3 / 54.2 for 1024; error
+//          1.49e-7 and 1.50e-7, with squared powers 1.69e-7)
 template <int N>
 constexpr int row_shape(int half, long long batch) {
     if (N == 1024) return half ? (batch <= 4096 || batch >= 12288 ? 4 : 0) : (batch <= 3072 ? 4 : 1);
     if (N == 2048 && half && batch <= 511) return 4;
     if (N == 4096 && half && batch <= 2048) return 1;
     if (N == 8192 && !half && batch <= 4096) return 8;
-    if (N == 16384 && !half && batch <= 512) return 7;
+    if (N == 16384 && !half && batch <= 127) return 7;
     return Configs<N>::kRowDefault[half];
 }
 

@@ -130,7 +130,7 @@ def test_rows_by_batch(api, storage, n, batch):
 
 @pytest.mark.parametrize("storage", [0, 1])
 @pytest.mark.parametrize("n,batch", [(1024, 3072), (1024, 3073), (1024, 4096), (1024, 4097), (1024, 12287),
-                                     (1024, 12289), (4096, 2048), (4096, 2049)])
+                                     (1024, 12289), (4096, 2048), (4096, 2049), (16384, 127), (16384, 128)])
 def test_rows_by_batch_limits(api, storage, n, batch):
     """Both sides of the remaining batch limits of the row shapes."""
     test_rows_by_batch(api, storage, n, batch)
