@@ -172,8 +172,8 @@ struct Configs<4096> {
     // against 6,298, where a call without them leaves its write-back for later)
     // FP16 rows: the second stage's factors from LDS, 13.5 against 15.2 us for
     // 2^23 points, 47.9 / 53.3 for 2^25
-    // matched rows: the same for the SAR chain (142.3-143.1 against 146.9-148.3
-    // us, FP16 125.4-126.1 / 125.5-125.8), not for the range-Doppler one (RdRows)
+    // matched rows: the same, SAR chain 145.0 against 148.0 us (FP16 123.0 /
+    // 124.2), range-Doppler chain 200.6-201.1 / 199.9-200.7 (FP16 178.3 / 182.8)
     // matched columns (the SAR azimuth pass): bound by the 64-byte pieces of
     // the image rows (128 MiB strided reads alone take 34 us, writes 24 us);
     // the 4-column strips' 32-byte pieces cost more.  Image after image, on
@@ -246,19 +246,6 @@ struct Configs<16384> {
                            KCfg<16384, 32, 1, false, XCHG_HALF, 1, false, Radices<16, 16, 16, 4>>,
                            KCfg<16384, 16, 1, false, XCHG_HALF, 1, false, Radices<16, 16, 16, 4>>>;
     static constexpr int kRowMatched[2] = {4, 4};
-};
-
-// The matched rows of the range-Doppler chain: at 4096 points with FP32
-// intermediates the squared powers, 203.5-204.2 against 204.6-205.5 us per
-// chain with the second stage's factors from LDS; with FP16 the latter
-// (183.8 against 186.4 us).
-template <int N>
-struct RdRows {
-    static constexpr int v[2] = {Configs<N>::kRowMatched[0], Configs<N>::kRowMatched[1]};
-};
-template <>
-struct RdRows<4096> {
-    static constexpr int v[2] = {1, 9};
 };
 
 // The row shape of a plain transform (index into Rows) by its storage and
@@ -502,7 +489,7 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
     const bool mf = epi == EPI_MATCHED || epi == EPI_MATCHED_Y;
     if (layout == LAYOUT_ROWS) {
         const int v = variant >= 0 ? variant
-                      : mf         ? (a.rd_chain ? RdRows<N>::v[half] : Configs<N>::kRowMatched[half])
+                      : mf         ? Configs<N>::kRowMatched[half]
                                    : row_shape<N>(half, a.batch);
         return with_variant(v, typename Configs<N>::Rows{}, f);
     }

@@ -175,7 +175,6 @@ struct KArgs {
     float ref_scale[2];
     unsigned long long *ref_flag;
     unsigned long long ref_epoch;
-    int rd_chain;  // the range pass of the range-Doppler chain (its own row shape)
     // Any kernel: workgroup 0 first stores 0 to *clear_flag (a pass that
     // runs after the one that waited on it, so no reader remains).
     unsigned long long *clear_flag;

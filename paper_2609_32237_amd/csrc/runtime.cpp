@@ -1062,7 +1062,6 @@ int sar_rd_form_image(int64_t n_az, int64_t n_rg, int inter_storage, const sar_g
     //    pass's workgroup 0 computes it (a row shape that cannot falls back
     //    to a launch of its own).
     KArgs ar{n_az, 1, n_rg, n_rg, 1.0f, 0};
-    ar.rd_chain = 1;
     ar.ref_rows = 1;
     ar.ref_in[0] = reinterpret_cast<const float2 *>(range_ref);
     ar.ref_out[0] = h_rg;
@@ -1075,8 +1074,7 @@ int sar_rd_form_image(int64_t n_az, int64_t n_rg, int inter_storage, const sar_g
         const KArgs aref{1, 1, n_rg, n_rg, s_rg, 0};
         e = launch_fft(n_rg, vrow, LAYOUT_ROWS, 0, 0, 0, EPI_NONE, range_ref, h_rg, tw_rg, nullptr, aref, stream);
         if (e != hipSuccess) return map_hip(e);
-        KArgs ar2{n_az, 1, n_rg, n_rg, 1.0f, 0};
-        ar2.rd_chain = 1;
+        const KArgs ar2{n_az, 1, n_rg, n_rg, 1.0f, 0};
         e = launch_fft(n_rg, vrow, LAYOUT_ROWS, FFT_STORAGE_FP32, inter_storage, 0, EPI_MATCHED, raw, out, tw_rg,
                        h_rg, ar2, stream);
     }
