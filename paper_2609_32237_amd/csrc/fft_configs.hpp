@@ -306,8 +306,9 @@ constexpr int row_shape(int half, long long batch) {
 //   4096  250 columns 14.8 (4 columns, 1024 threads) / 19.0 (8 columns, 64
 //         points), 1000 18.1 / 19.2, 1536 46.9 / 32.0; SAR over 1024 columns
 //         52.5 / 56.9, over 4096 157 (4 columns, 64 points) / 145
-//   8192  in place: 100 columns 20.6 / 23.0 (2 / 4 columns), 1000 61.3 / 41.9
-//         (44.1 with 64 points), 4096 332 / 248 (234); SAR over 1024 98.0 /
+//   8192  in place: 100 columns 23.2 / 25.6 (2 / 4 columns), 512 33.3 / 40.2
+//         (256 strips of 2), 700 50.6 / 38.9, 1000 56.1 / 41.4 (43.5 with 64
+//         points), 4096 290 / 237 (214); SAR over 1024 98.0 /
 //         95.8 (94.5), 2048 238 / 194 (177); range-Doppler FP32 238 / 244
 //   16384 in place: 100 columns 35.6 / 36.6 (1 / 2), 1000 212 / 123; SAR over
 //         1024 266 / 202, range-Doppler 298 / 278
@@ -332,7 +333,7 @@ constexpr int column_shape(int use, int half, long long columns) {
     }
     if (N == 8192) {
         if (use == COLS_SCALED) return half ? 1 : 2;
-        if (use == COLS_PLAIN && columns < 512) return 2;
+        if (use == COLS_PLAIN && columns <= 512) return 2;
         return half || (use == COLS_PLAIN && columns <= 1024) ? 1 : 0;
     }
     if (N == 16384) return use == COLS_PLAIN && columns < 256 ? 1 : 0;

@@ -134,3 +134,10 @@ def test_rows_by_batch(api, storage, n, batch):
 def test_rows_by_batch_limits(api, storage, n, batch):
     """Both sides of the remaining batch limits of the row shapes."""
     test_rows_by_batch(api, storage, n, batch)
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("n,count", [(8192, 512), (8192, 513)])
+def test_long_columns_at_the_strip_limit(api, storage, n, count):
+    """512 columns of 8192 points: 256 strips of two."""
+    test_long_columns_in_place(api, storage, n, count)
