@@ -294,7 +294,9 @@ constexpr int row_shape(int half, long long batch) {
 // that no cache holds:
 //   256   pass of 16384 columns 12.7 / 14.2 (16 / 32 columns a strip), of
 //         65536 55.3 / 53.8 and, in FP16, 38.7 / 34.1
-//   512   16384 columns 30.2 / 26.9 (FP16 17.9 / 18.8), 65536 FP16 73.2 / 70.3
+//   512   both passes of 2^18 points: 16384 columns 54.6 / 54.8 (FP16 36.6 /
+//         38.1), 32768 97.7 / 98.1 (FP16 68.3 / 64.3), 49664 145.6 / 151.6
+//         (FP16 96.7 / 99.2), 65536 206.8 / 198.6 (FP16 125.3 / 122.7)
 //   1024  4096 columns 14.1 / 14.3, 8192 38.3 / 30.3, 16384 81.9 / 67.9 (FP16
 //         48.7 / 41.9); SAR over 8192 columns 78.1 / 80.1, 16384 162.5 / 154.3
 //   2048  (4, 8 and twice 16 points; 8 and 16 columns with 64 points) 1000
@@ -315,7 +317,8 @@ constexpr int row_shape(int half, long long batch) {
 enum { COLS_PLAIN, COLS_TWIDDLED, COLS_SCALED, COLS_MATCHED };
 template <int N>
 constexpr int column_shape(int use, int half, long long columns) {
-    if (N == 256 || N == 512) return columns >= 32768 ? 1 : 0;
+    if (N == 256) return columns >= 32768 ? 1 : 0;
+    if (N == 512) return columns >= (half ? 32768 : 65536) ? 1 : 0;
     if (N == 1024) {
         if (use != COLS_MATCHED) return columns >= 8192 ? 1 : 0;
         return (half ? 0 : 3) + (columns >= 16384 ? 1 : 0);

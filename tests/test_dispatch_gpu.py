@@ -141,3 +141,22 @@ def test_rows_by_batch_limits(api, storage, n, batch):
 def test_long_columns_at_the_strip_limit(api, storage, n, count):
     """512 columns of 8192 points: 256 strips of two."""
     test_long_columns_in_place(api, storage, n, count)
+
+
+@pytest.mark.parametrize("log2n,batch", [(17, 255), (17, 256), (18, 128)])
+def test_long_transforms_at_the_strip_limits(api, log2n, batch):
+    """FP32 passes of 512-point columns around 65536 of them."""
+    import torch
+
+    n = 1 << log2n
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    x = torch.view_as_complex(torch.empty(batch, n, 2, device="cuda").uniform_(-1.0, 1.0, generator=g))
+    plan = api.Plan(n, batch, 1, n, 0, -1)
+    y = plan.execute(x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    plan.close()
+    pick = np.unique([0, batch // 2, batch - 1])
+    at = torch.from_numpy(pick).cuda()
+    e = rel_rows(widen(to_host(y[at])), oracle.fft(to_host(x[at]))).max()
+    log(f"long 2^{log2n} x {batch}: rel {e:.2e}")
+    assert e < TOL[0]
