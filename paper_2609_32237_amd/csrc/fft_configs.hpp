@@ -282,7 +282,7 @@ constexpr int row_shape(int half, long long batch) {
 }
 
 // The column shape of a pass over `columns` columns in all (every problem of
-// the grid counted), by what the pass does:
+// the grid counted), `row` of them side by side, by what the pass does:
 //   plain    the transform (and the last pass of the split forms);
 //   twiddled the four-step epilogues (at most 32 points per thread);
 //   scaled   the range-Doppler chain's azimuth pass, written transposed;
@@ -305,6 +305,9 @@ constexpr int row_shape(int half, long long batch) {
 //         83.4, 57.6; 16384 356, 233, 177, 156 (FP16 191, 164, 106, 82.3);
 //         SAR over 1024 32.1, 35.2, 39.2, 43.8; 4096 93.5, 74.8, 76.2, 80.4
 //         (FP16 86.7, 69.7, 66.2, 72.4), 8192 209, 167, 154, 157
+//         The second pass of 2^22 points, FP32, in rows of 2048 columns: 8
+//         columns (16 points) against 16, whole transforms: 3 of them 89.7 /
+//         99.9, 8 236 / 248, 16 463 / 463, 32 904 / 892
 //   4096  250 columns 14.8 (4 columns, 1024 threads) / 19.0 (8 columns, 64
 //         points), 1000 18.1 / 19.2, 1536 46.9 / 32.0; SAR over 1024 columns
 //         52.5 / 56.9, over 4096 157 (4 columns, 64 points) / 145
@@ -316,7 +319,7 @@ constexpr int row_shape(int half, long long batch) {
 //         1024 266 / 202, range-Doppler 298 / 278
 enum { COLS_PLAIN, COLS_TWIDDLED, COLS_SCALED, COLS_MATCHED };
 template <int N>
-constexpr int column_shape(int use, int half, long long columns) {
+constexpr int column_shape(int use, int half, long long columns, long long row) {
     if (N == 256) return columns >= 32768 ? 1 : 0;
     if (N == 512) return columns >= (half ? 32768 : 65536) ? 1 : 0;
     if (N == 1024) {
@@ -326,8 +329,9 @@ constexpr int column_shape(int use, int half, long long columns) {
     if (N == 2048) {
         if (columns < 2048 || (use == COLS_SCALED && columns < 4096)) return 0;
         if (columns < 4096 || use == COLS_TWIDDLED) return 1;
-        if (use == COLS_PLAIN) return half && columns < 8192 ? 2 : 3;
-        return half || columns >= 8192 ? 2 : 1;
+        if (use != COLS_PLAIN) return half || columns >= 8192 ? 2 : 1;
+        if (half) return columns < 8192 ? 2 : 3;
+        return row < 4096 && columns < 32768 ? 1 : 3;
     }
     if (N == 4096) {
         if (use == COLS_TWIDDLED) return 3;
@@ -503,7 +507,7 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
                     : epi == EPI_SCALE   ? COLS_SCALED
                     : epi == EPI_MATCHED ? COLS_MATCHED
                                          : COLS_TWIDDLED;
-    const int v = variant >= 0 ? variant : column_shape<N>(use, half, columns);
+    const int v = variant >= 0 ? variant : column_shape<N>(use, half, columns, a.batch);
     return with_variant(v, Cols{}, f);
 }
 

@@ -143,9 +143,10 @@ def test_long_columns_at_the_strip_limit(api, storage, n, count):
     test_long_columns_in_place(api, storage, n, count)
 
 
-@pytest.mark.parametrize("log2n,batch", [(17, 255), (17, 256), (18, 128)])
+@pytest.mark.parametrize("log2n,batch", [(17, 255), (17, 256), (18, 128), (22, 15), (22, 16)])
 def test_long_transforms_at_the_strip_limits(api, log2n, batch):
-    """FP32 passes of 512-point columns around 65536 of them."""
+    """FP32 passes of 512-point columns around 65536 of them, and of 2048-point
+    columns in rows of 2048 around 32768."""
     import torch
 
     n = 1 << log2n
