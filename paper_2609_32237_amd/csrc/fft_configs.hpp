@@ -112,10 +112,10 @@ struct Configs<2048> {
                        KCfg<2048, 16, 1, false, XCHG_FULL, 1, false, Radices<16, 16, 8>>>;
     using Cols = KList<KCfg<2048, 16, 4, true, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
                        KCfg<2048, 16, 8, true, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
+                       KCfg<2048, 16, 4, true, XCHG_FULL, 0, false, Radices<16, 16, 8>>,
                        // 64 points per thread: one exchange, whole lines with 16 columns
                        KCfg<2048, 64, 8, true, XCHG_SPLIT, 1, false, Radices<64, 32>>,
-                       KCfg<2048, 64, 16, true, XCHG_SPLIT, 1, false, Radices<64, 32>>,
-                       KCfg<2048, 16, 4, true, XCHG_FULL, 0, false, Radices<16, 16, 8>>>;
+                       KCfg<2048, 64, 16, true, XCHG_SPLIT, 1, false, Radices<64, 32>>>;
     // 32 points per thread: 228 against 241 us (16 points, 8 range bins) and
     // 247 us (16 points, 4 range bins) for a 2048 x 8192 range-Doppler chain
     // with FP32 intermediates, 199 against 197 and 212 us with FP16
@@ -329,12 +329,11 @@ constexpr int column_shape(int use, int half, long long columns, long long row) 
     if (N == 2048) {
         if (columns < 2048 || (use == COLS_SCALED && columns < 4096)) return 0;
         if (columns < 4096 || use == COLS_TWIDDLED) return 1;
-        if (use != COLS_PLAIN) return half || columns >= 8192 ? 2 : 1;
-        if (half) return columns < 8192 ? 2 : 3;
-        return row < 4096 && columns < 32768 ? 1 : 3;
+        if (use != COLS_PLAIN) return half || columns >= 8192 ? 3 : 1;
+        if (half) return columns < 8192 ? 3 : 4;
+        return row < 4096 && columns < 32768 ? 1 : 4;
     }
     if (N == 4096) {
-        if (use == COLS_TWIDDLED) return 3;
         if (use == COLS_SCALED) return 6;  // 4 columns: written transposed, 206 against 214 us (8 columns) per chain
         return columns <= 1024 ? 2 : 5;
     }
@@ -354,6 +353,30 @@ struct KListSize<KList<Ks...>> {
     static constexpr int value = sizeof...(Ks);
 };
 
+// The four-step epilogues hold at most 32 points per thread and run on columns
+// of at most 2048 points: the leading shapes of each list that fit (the
+// shapes a plan may force for its twiddled passes).
+constexpr int kMaxTwiddledN = 2048;
+template <int N, class... Ks>
+constexpr int twiddled_shapes(KList<Ks...>) {
+    constexpr int points[] = {Ks::P...};
+    int k = 0;
+    while (N <= kMaxTwiddledN && k < (int)sizeof...(Ks) && points[k] <= 32) ++k;
+    return k;
+}
+// column_shape stays among them on both sides of every power of two
+template <int N>
+constexpr bool twiddled_shapes_fit() {
+    if (N > kMaxTwiddledN) return true;
+    const int most = twiddled_shapes<N>(typename Configs<N>::Cols{});
+    for (int half = 0; half < 2; ++half)
+        for (int l = 0; l <= 40; ++l)
+            for (int d = -1; d <= 1; ++d)
+                for (long long row : {(1LL << l) + d, 64LL})
+                    if (column_shape<N>(COLS_TWIDDLED, half, (1LL << l) + d, row) >= most) return false;
+    return true;
+}
+
 // Calls f(K{}) for the idx-th entry of the list.
 template <class F, class K, class... Ks>
 hipError_t with_variant(int idx, KList<K, Ks...>, F &&f) {
@@ -372,10 +395,11 @@ hipError_t with_variant(int idx, KList<K, Ks...>, F &&f) {
 //               columns read FP32 or FP16 and write FP32 (azimuth compression);
 //   scaled:     columns, forward, input storage == output storage (the azimuth
 //               FFT of the full range-Doppler chain);
-//   twiddled:   columns, either direction, input storage == output storage,
-//               written as rows (first pass of a four-step transform), or
-//               written in place with the factor keyed by the second grid
-//               axis (middle pass of a three-pass transform);
+//   twiddled:   columns of at most 2048 points, either direction, input
+//               storage == output storage, written as rows (first pass of a
+//               four-step transform), or written in place with the factor
+//               keyed by the second grid axis (middle pass of a three-pass
+//               transform); matched with such factors at 128 points;
 //   RCMC:       the Rcmc list (row-mapped, several transforms per workgroup),
 //               inverse, read FP32 or FP16, write FP32 columns (migration
 //               correction, azimuth filter and azimuth inverse FFT).
@@ -400,7 +424,7 @@ hipError_t dispatch_cfg_full(int in_st, int out_st, int inv, int epi, const void
         }
     }
     if (epi == EPI_TWIDDLE) {
-        if constexpr (K::COLS && !K::PERSIST && K::P <= 32) {
+        if constexpr (K::COLS && !K::PERSIST && K::P <= 32 && K::N <= kMaxTwiddledN) {
             if (in_st != out_st) return hipErrorInvalidValue;
             if (in_st == 0)
                 return inv ? launch_one<K, 0, 0, true, EPI_TWIDDLE>(in, out, tw, spec, a, s)
@@ -412,7 +436,7 @@ hipError_t dispatch_cfg_full(int in_st, int out_st, int inv, int epi, const void
         }
     }
     if (epi == EPI_TWIDDLE_Y) {
-        if constexpr (K::COLS && !K::PERSIST && K::P <= 32) {
+        if constexpr (K::COLS && !K::PERSIST && K::P <= 32 && K::N <= kMaxTwiddledN) {
             if (in_st != out_st) return hipErrorInvalidValue;
             if (in_st == 0)
                 return inv ? launch_one<K, 0, 0, true, EPI_TWIDDLE_Y>(in, out, tw, spec, a, s)
@@ -424,7 +448,7 @@ hipError_t dispatch_cfg_full(int in_st, int out_st, int inv, int epi, const void
         }
     }
     if (epi == EPI_MATCHED_Y) {
-        if constexpr (K::COLS && !K::PERSIST && K::P <= 32) {
+        if constexpr (K::COLS && !K::PERSIST && K::N == 128) {  // the split azimuth pass: 16384 = 128 x 128
             if (inv || in_st != 0 || out_st != 0) return hipErrorInvalidValue;
             return launch_one<K, 0, 0, false, EPI_MATCHED_Y>(in, out, tw, spec, a, s);
         } else {
@@ -494,14 +518,14 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
         }
     }
     const int half = (in_st | out_st) != 0;  // any FP16 storage involved
-    const bool mf = epi == EPI_MATCHED || epi == EPI_MATCHED_Y;
     if (layout == LAYOUT_ROWS) {
-        const int v = variant >= 0 ? variant
-                      : mf         ? Configs<N>::kRowMatched[half]
-                                   : row_shape<N>(half, a.batch);
+        const int v = variant >= 0         ? variant
+                      : epi == EPI_MATCHED ? Configs<N>::kRowMatched[half]
+                                           : row_shape<N>(half, a.batch);
         return with_variant(v, typename Configs<N>::Rows{}, f);
     }
     using Cols = typename Configs<N>::Cols;
+    static_assert(twiddled_shapes_fit<N>(), "the four-step epilogues hold at most 32 points per thread");
     const long long columns = a.batch * (a.outer > 1 ? a.outer : 1) * (a.outer2 > 1 ? a.outer2 : 1);
     const int use = epi == EPI_NONE      ? COLS_PLAIN
                     : epi == EPI_SCALE   ? COLS_SCALED
@@ -513,10 +537,11 @@ hipError_t dispatch(int variant, int layout, int in_st, int out_st, int inv, int
 
 template <int N>
 int variant_count(int layout) {
-    return layout == LAYOUT_ROWS   ? KListSize<typename Configs<N>::Rows>::value
-           : layout == LAYOUT_COLS ? KListSize<typename Configs<N>::Cols>::value
-           : layout == LAYOUT_RCMC ? KListSize<typename Configs<N>::Rcmc>::value
-                                   : KListSize<typename Configs<N>::RowsHalf>::value;
+    return layout == LAYOUT_ROWS            ? KListSize<typename Configs<N>::Rows>::value
+           : layout == LAYOUT_COLS          ? KListSize<typename Configs<N>::Cols>::value
+           : layout == LAYOUT_COLS_TWIDDLED ? twiddled_shapes<N>(typename Configs<N>::Cols{})
+           : layout == LAYOUT_RCMC          ? KListSize<typename Configs<N>::Rcmc>::value
+                                            : KListSize<typename Configs<N>::RowsHalf>::value;
 }
 
 }  // namespace mi355fft

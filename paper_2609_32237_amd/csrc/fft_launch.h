@@ -34,7 +34,9 @@ hipError_t launch_kernel(void (*kern)(Params...), dim3 grid, dim3 block, hipStre
 // The row kernels with the binary16 exchange (Section VII's FP16-exchange
 // variant: half the LDS of the FP32 exchange in one round, about 6 dB less
 // accurate) form a fourth family, for FP16 storage only.
-enum { LAYOUT_ROWS = 0, LAYOUT_COLS = 1, LAYOUT_RCMC = 2, LAYOUT_ROWS_HALF = 3 };
+// (LAYOUT_COLS_TWIDDLED only counts variants: the column shapes that the
+// four-step epilogues take)
+enum { LAYOUT_ROWS = 0, LAYOUT_COLS = 1, LAYOUT_RCMC = 2, LAYOUT_ROWS_HALF = 3, LAYOUT_COLS_TWIDDLED = 4 };
 // Per-kernel fusions around the transform:
 //   EPI_NONE     the plain transform;
 //   EPI_MATCHED  forward, X * conj(spec), inverse (range or azimuth

@@ -312,10 +312,12 @@ int variant_count(int64_t n, int layout) {
 // Kernel-shape override for tests and tuning: MI355FFT_ROW_VARIANT /
 // MI355FFT_COL_VARIANT / MI355FFT_RCMC_VARIANT = index into the size's list of
 // row, column or migration-correction kernels (unset: default).
-// Returns -1 for the default, -2 for an index the size does not have.
+// Returns -1 for the default, -2 for an index the size (or, for a four-step
+// transform's twiddled pass, that pass) does not have.
 int chosen_variant(int64_t n, int layout) {
+    const bool cols = layout == mi355fft::LAYOUT_COLS || layout == mi355fft::LAYOUT_COLS_TWIDDLED;
     const char *e = std::getenv(layout == mi355fft::LAYOUT_ROWS   ? "MI355FFT_ROW_VARIANT"
-                                : layout == mi355fft::LAYOUT_COLS ? "MI355FFT_COL_VARIANT"
+                                : cols                            ? "MI355FFT_COL_VARIANT"
                                 : layout == mi355fft::LAYOUT_RCMC ? "MI355FFT_RCMC_VARIANT"
                                                                   : "MI355FFT_HALF_VARIANT");
     if (!e || !e[0]) return -1;
@@ -476,9 +478,9 @@ int fft_plan_create_ex(int64_t n, int64_t batch, int64_t stride, int64_t dist, i
     const int64_t n1 = split ? n / n2 : 0;
     const int64_t na = three ? int64_t(1) << (ilog2(n2) / 2) : 0, nb = three ? n2 / na : 0;
     const int variant = four_step ? -1 : chosen_variant(n, layout);
-    const int v1 = split ? chosen_variant(n1, mi355fft::LAYOUT_COLS) : -1;
+    const int v1 = split ? chosen_variant(n1, mi355fft::LAYOUT_COLS_TWIDDLED) : -1;
     const int v2 = split && !three ? chosen_variant(n2, mi355fft::LAYOUT_COLS) : -1;
-    const int va = three ? chosen_variant(na, mi355fft::LAYOUT_COLS) : -1;
+    const int va = three ? chosen_variant(na, mi355fft::LAYOUT_COLS_TWIDDLED) : -1;
     const int vb = three ? chosen_variant(nb, mi355fft::LAYOUT_COLS) : -1;
     if (variant == -2 || v1 == -2 || v2 == -2 || va == -2 || vb == -2) return FFT_EINVAL;
     if (four_step && batch > (int64_t)0x7fffffff) return FFT_EUNSUPPORTED;
