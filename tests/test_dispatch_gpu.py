@@ -161,3 +161,35 @@ def test_long_transforms_at_the_strip_limits(api, log2n, batch):
     e = rel_rows(widen(to_host(y[at])), oracle.fft(to_host(x[at]))).max()
     log(f"long 2^{log2n} x {batch}: rel {e:.2e}")
     assert e < TOL[0]
+
+
+RD_SHAPES = {
+    (1024, 8192): dict(pulse_samples=600, targets=((256, 300, 1.0), (512, 4400, 1.0), (768, 7000, 0.6))),
+    (1024, 16384): dict(pulse_samples=600, targets=((256, 300, 1.0), (512, 15000, 1.0))),
+    (2048, 4096): dict(prf=250.0, targets=((512, 128, 1.0), (1024, 2640, 1.0), (1536, 3384, 0.8))),
+    (2048, 8192): dict(prf=250.0, targets=((512, 128, 1.0), (1024, 5640, 1.0), (1536, 7384, 0.8))),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(RD_SHAPES))
+def test_range_doppler_by_shape(api, shape):
+    """The scaled azimuth pass, written transposed, on both sides of its strip
+    limits (1024 pulses from 8192 range bins, 2048 from 4096 and 8192), and the
+    range pass at 8192 and 16384 bins; each with either intermediate."""
+    import torch
+
+    n_az, n_rg = shape
+    args = dict(prf=125.0)
+    args.update(RD_SHAPES[shape])
+    sc = workloads.rd_scene_small(n_az=n_az, n_rg=n_rg, **args)
+    ref = oracle.rd_chain(sc.raw, sc.range_ref, sc.geometry)
+    raw, range_ref = to_dev(sc.raw), to_dev(sc.range_ref)
+    for inter in (0, 1):
+        got = to_host(api.sar_rd_form_image(raw, range_ref, sc.geometry, inter))
+        torch.cuda.synchronize()
+        e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+        log(f"rd {n_az} x {n_rg} inter {inter}: rel {e:.2e}")
+        assert e < TOL[inter]
+        for a, r in zip(sc.targets_az, sc.targets_rg):
+            win = np.abs(got[a - 8:a + 9, r - 8:r + 9])
+            assert np.unravel_index(np.argmax(win), win.shape) == (8, 8), (a, r)
