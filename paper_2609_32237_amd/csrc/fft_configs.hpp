@@ -3,14 +3,16 @@
 // Shapes (points per thread P, transforms per workgroup C, radix sequence,
 // exchange mode, twiddle mode, persistence) are chosen for gfx950: wave64,
 // 160 KiB LDS per CU, 512 VGPRs per SIMD lane.  Rows keep one transform per
-// 256-512 threads; columns keep a strip of C adjacent columns so each row
+// 64-1024 threads; columns keep a strip of C adjacent columns so each row
 // access is a C-element segment.  The paper's M6 schedules (Section VI:
 // 16-8-8-8 for 8192 and 16-16-8-8 for 16384, 16 values per thread) were
 // shaped by a 32 KiB threadgroup buffer; these use larger radices because the
 // LDS is five times larger.
 //
-// Each size lists its variants; index 0 of each list is the default.  Every
-// variant computes the same transform, and the tests force each of them.
+// Each size lists its variants.  row_shape, kRowMatched and column_shape name
+// the one that a call takes (the migration pass and the rows with the binary16
+// exchange take index 0 of theirs).  Every variant computes the same
+// transform, and the tests force each of them.
 #pragma once
 
 #include "fft_kernel.hpp"
@@ -98,8 +100,9 @@ struct Configs<1024> {
                        KCfg<1024, 16, 4, false, XCHG_SPLIT, 1, false, Radices<16, 16, 4>>>;
     using RowsHalf = KList<KCfg<1024, 16, 4, false, XCHG_HALF, 1, false, Radices<16, 16, 4>>>;
     // (plain rows go by their batch, row_shape)
-    // matched: one transform, one wave, per workgroup, SAR 1024 x 1024 21.0 /
-    // 21.9 us, 4096 x 1024 50.4 / 51.2
+    // matched: one transform, one wave, per workgroup against four of each, SAR
+    // 1024 x 1024 25.2 / 27.0 us, 4096 x 1024 50.2 / 51.2, range-Doppler 31.8 /
+    // 32.8 and 74.8 / 76.7
     static constexpr int kRowDefault[2] = {1, 0};
     static constexpr int kRowMatched[2] = {4, 4};
 };
@@ -122,9 +125,10 @@ struct Configs<2048> {
     using Rcmc = KList<KCfg<2048, 32, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>,
                        KCfg<2048, 16, 8, false, XCHG_SPLIT, 1, false, Radices<16, 16, 8>>>;
     using RowsHalf = KList<KCfg<2048, 16, 2, false, XCHG_HALF, 1, false, Radices<16, 16, 8>>>;
-    // FP32: one transform per workgroup (88.5 against 91.4 us for 2^25 points,
-    // 20.1 / 20.6 for 2^23; FP16 50.4 / 52.2 but 14.2 / 13.7), matched too (SAR
-    // 4096 x 2048 81.6 / 85.4 us, FP16 76.6 / 74.6)
+    // FP32: one transform per workgroup against two (88.7 / 91.2 us for 2^25
+    // points, 25.6 / 25.9 for 2^23; FP16 50.8 / 51.7, but 16.2 / 14.4 for 2^23
+    // and 187 / 183 for 2^27), matched too (SAR 4096 x 2048 81.6 / 84.1 us,
+    // FP16 75.2 / 73.9; range-Doppler 111.5 / 114.3, FP16 98.2 / 97.6)
     static constexpr int kRowDefault[2] = {4, 0};
     static constexpr int kRowMatched[2] = {4, 0};
 };
@@ -170,15 +174,15 @@ struct Configs<4096> {
     // FP32 rows: with the rows' XCD groups, streaming stores win back to back
     // (6,108-6,171 against 6,015-6,027 GB/s, same process; flushed 6,120
     // against 6,298, where a call without them leaves its write-back for later)
-    // FP16 rows: the second stage's factors from LDS, 13.5 against 15.2 us for
-    // 2^23 points, 47.9 / 53.3 for 2^25
+    // FP16 rows: the second stage's factors from LDS, 27.8 against 29.9 us for
+    // 2^24 points, 49.2 / 53.4 for 2^25 (smaller batches: row_shape)
     // matched rows: the same, SAR chain 145.0 against 148.0 us (FP16 123.0 /
     // 124.2), range-Doppler chain 200.6-201.1 / 199.9-200.7 (FP16 178.3 / 182.8)
     // matched columns (the SAR azimuth pass): bound by the 64-byte pieces of
     // the image rows (128 MiB strided reads alone take 34 us, writes 24 us);
     // the 4-column strips' 32-byte pieces cost more.  Image after image, on
-    // inputs that no cache holds, an FP32 chain takes 145 us with 8 columns
-    // and 157 with 4 (FP16 124 and 128); a single chain after a flush, where
+    // inputs that no cache holds, an FP32 chain takes 146 us with 8 columns
+    // and 152 with 4 (FP16 124 and 132); a single chain after a flush, where
     // the intermediate is still in the Infinity Cache, 141 and 135.
     static constexpr int kRowDefault[2] = {8, 9};
     static constexpr int kRowMatched[2] = {9, 9};
@@ -213,8 +217,9 @@ struct Configs<8192> {
     // the second stage's factors from LDS, 5,740 against 5,607 GB/s flushed
     // and 5,700-5,731 against 5,318-5,604 back to back (same box, one run)
     static constexpr int kRowDefault[2] = {7, 4};
-    // matched: three stages too (SAR 1024 x 8192 75.1 against 80.9 us and, with
-    // an FP16 intermediate, 68.4 against 72.3; range-Doppler 101.8 / 106.9)
+    // matched: three stages too (SAR 1024 x 8192 79.2 against 83.7 us and, with
+    // an FP16 intermediate, 69.1 / 74.0; 2048 x 8192 155 / 154 and 132.5 /
+    // 138.3; range-Doppler 102.9 / 110.3 and 90.6 / 95.1)
     static constexpr int kRowMatched[2] = {4, 4};
 };
 template <>
@@ -292,49 +297,55 @@ constexpr int row_shape(int half, long long batch) {
 // there are strips enough for the 256 CUs; with fewer columns narrow strips
 // keep more CUs busy.  Times in us, narrower against wider shape, on inputs
 // that no cache holds:
-//   256   pass of 16384 columns 12.7 / 14.2 (16 / 32 columns a strip), of
-//         65536 55.3 / 53.8 and, in FP16, 38.7 / 34.1
-//   512   both passes of 2^18 points: 16384 columns 54.6 / 54.8 (FP16 36.6 /
-//         38.1), 32768 97.7 / 98.1 (FP16 68.3 / 64.3), 49664 145.6 / 151.6
-//         (FP16 96.7 / 99.2), 65536 206.8 / 198.6 (FP16 125.3 / 122.7)
-//   1024  4096 columns 14.1 / 14.3, 8192 38.3 / 30.3, 16384 81.9 / 67.9 (FP16
-//         48.7 / 41.9); SAR over 8192 columns 78.1 / 80.1, 16384 162.5 / 154.3
-//   2048  (4, 8 and twice 16 points; 8 and 16 columns with 64 points) 1000
-//         columns 11.3, 11.9, 12.9, 17.0; 2048 17.5, 15.8, 16.8, 20.3; 4096
-//         59.8, 43.6, 39.6, 29.2 (FP16 25.9, 20.0, 18.1, 19.6); 8192 143, 104,
-//         83.4, 57.6; 16384 356, 233, 177, 156 (FP16 191, 164, 106, 82.3);
-//         SAR over 1024 32.1, 35.2, 39.2, 43.8; 4096 93.5, 74.8, 76.2, 80.4
-//         (FP16 86.7, 69.7, 66.2, 72.4), 8192 209, 167, 154, 157
+//   256   both passes of 2^16 points (16 / 32 columns a strip): 16384 columns
+//         29.7 / 30.8, 32768 52.5 / 53.2 (FP16 34.4 / 33.1), 65536 100.4 /
+//         97.0 (FP16 63.7 / 59.4)
+//   512   both passes of 2^18 points (16 / 32): 16384 columns 54.6 / 54.8 (FP16
+//         36.6 / 38.1), 32768 97.7 / 98.1 (FP16 68.3 / 64.3), 49664 145.6 /
+//         151.6 (FP16 96.7 / 99.2), 65536 206.8 / 198.6 (FP16 125.3 / 122.7)
+//   1024  (8 / 16) 3000 columns 15.4 / 14.9, 4096 18.1 / 15.0 but 4100 17.5 /
+//         20.4, 6000 25.1 / 26.3 (FP16 18.0 / 16.6), 8192 39.0 / 29.2, 16384
+//         82.9 / 70.5 (FP16 50.2 / 41.4); SAR over 4096 columns 42.0 / 43.8,
+//         8192 79.4 / 76.6 (FP16 69.3 / 69.2), 16384 163 / 152 (135 / 131);
+//         range-Doppler over 8192 104.0 / 102.8 (FP16 90.7 / 90.2)
+//   2048  (4 and 8 columns of 16 points per thread, 8 and 16 of 64) 1000
+//         columns 13.8, 14.7, 15.9, 21.1; 2048 24.4, 18.4, 19.3, 23.2; 4096
+//         65.5, 44.2, 39.3, 28.7 (FP16 29.3, 24.8, 24.0, 21.4); 8192 145, 104,
+//         83.9, 58.4 (FP16 82.3, 68.2, 51.7, 48.3); 16384 358, 235, 179, 158
+//         (FP16 191, 166, 106, 87.8); SAR over 1024 31.9, 35.9, 39.2, 44.8;
+//         4096 93.4, 77.6, 73.8, 78.9 (FP16 86.5, 73.3, 67.8, 71.5); 8192 208,
+//         164, 155, 159; range-Doppler over 2048 61.4, 62.3, 64.5, 68.4; 4096
+//         102.8, 101.0, 103.0, 107.4 (FP16 98.5, 95.7, 95.4, 96.5); 8192 216,
+//         209, 208, 213 (FP16 176, 175, 177, 184)
 //         The second pass of 2^22 points, FP32, in rows of 2048 columns: 8
-//         columns (16 points) against 16, whole transforms: 3 of them 89.7 /
-//         99.9, 8 236 / 248, 16 463 / 463, 32 904 / 892
-//   4096  250 columns 14.8 (4 columns, 1024 threads) / 19.0 (8 columns, 64
-//         points), 1000 18.1 / 19.2, 1536 46.9 / 32.0; SAR over 1024 columns
-//         52.5 / 56.9, over 4096 157 (4 columns, 64 points) / 145
-//   8192  in place: 100 columns 23.2 / 25.6 (2 / 4 columns), 512 33.3 / 40.2
-//         (256 strips of 2), 700 50.6 / 38.9, 1000 56.1 / 41.4 (43.5 with 64
-//         points), 4096 290 / 237 (214); SAR over 1024 98.0 /
-//         95.8 (94.5), 2048 238 / 194 (177); range-Doppler FP32 238 / 244
-//   16384 in place: 100 columns 35.6 / 36.6 (1 / 2), 1000 212 / 123; SAR over
-//         1024 266 / 202, range-Doppler 298 / 278
+//         columns of 16 points against 16 of 64, whole transforms: 3 of them
+//         89.7 / 99.9, 8 236 / 248, 16 463 / 463, 32 904 / 892
+//   4096  (4 columns with 1024 threads / 8 of 64 points) 250 columns 20.0 /
+//         25.5, 1000 22.8 / 24.7, 1025 30.9 / 30.5, 1536 48.9 / 33.6; SAR over
+//         1024 columns 49.0 / 55.5, over 2048 95.1 / 80.6; range-Doppler (4 / 8
+//         columns of 64 points) over 1024 74.7 / 80.1, over 4096 201 / 209 (FP16
+//         182 / 182)
+//   8192  in place (2 / 4): 100 columns 23.2 / 25.6, 512 33.3 / 40.2 (256
+//         strips of 2), 700 50.6 / 38.9, 1000 56.1 / 41.4 (43.5 with 64
+//         points), 4096 290 / 237 (214); SAR over 1024 98.6 / 92.8 (93.0; FP16
+//         94.2 / 85.9, 90.1), 2048 235 / 197 (178); range-Doppler over 4096 630
+//         / 649, over 2048 244 / 245, FP16 216 / 210
+//   16384 in place (1 / 2): 100 columns 42.7 / 45.8, 200 47.8 / 46.4, 1000 208 /
+//         116; SAR over 1024 265 / 199, range-Doppler 284 / 274
 enum { COLS_PLAIN, COLS_TWIDDLED, COLS_SCALED, COLS_MATCHED };
 template <int N>
 constexpr int column_shape(int use, int half, long long columns, long long row) {
     if (N == 256) return columns >= 32768 ? 1 : 0;
     if (N == 512) return columns >= (half ? 32768 : 65536) ? 1 : 0;
-    if (N == 1024) {
-        if (use != COLS_MATCHED) return columns >= 8192 ? 1 : 0;
-        return (half ? 0 : 3) + (columns >= 16384 ? 1 : 0);
-    }
+    if (N == 1024) return (use == COLS_MATCHED && !half ? 3 : 0) + (columns >= 8192 ? 1 : 0);
     if (N == 2048) {
         if (columns < 2048 || (use == COLS_SCALED && columns < 4096)) return 0;
         if (columns < 4096 || use == COLS_TWIDDLED) return 1;
-        if (use != COLS_PLAIN) return half || columns >= 8192 ? 3 : 1;
-        if (half) return columns < 8192 ? 3 : 4;
-        return row < 4096 && columns < 32768 ? 1 : 4;
+        if (use == COLS_PLAIN) return !half && row < 4096 && columns < 32768 ? 1 : 4;
+        return use == COLS_MATCHED || half || columns >= 8192 ? 3 : 1;
     }
     if (N == 4096) {
-        if (use == COLS_SCALED) return 6;  // 4 columns: written transposed, 206 against 214 us (8 columns) per chain
+        if (use == COLS_SCALED) return 6;
         return columns <= 1024 ? 2 : 5;
     }
     if (N == 8192) {

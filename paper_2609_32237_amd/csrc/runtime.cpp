@@ -352,10 +352,15 @@ int64_t split_batch(int64_t n) {
 
 // Long strided columns (8192 or 16384 points, interleaved: dist 1) executed
 // out of place run as two passes of short columns: a 8192- or 16384-point
-// column kernel holds one or two columns per workgroup, so it reads 8- or
-// 16-byte pieces of each row, while 64- and 128-point column kernels hold
-// 32-64 columns.  A forced column shape (MI355FFT_COL_VARIANT) keeps the
-// single pass.
+// column kernel holds at most four or two columns per workgroup, so it reads
+// pieces of 32 or 16 bytes of each row (FP32), while 64- and 128-point column
+// kernels hold 32-64 columns.  Two passes against the best single one, us:
+// 8192 points x 100 13.5 / 25.6, x 400 24.9 / 30.9, x 700 40.2 / 40.1, x 1000
+// 54.0 / 42.7, x 2000 100 / 86.4, x 4096 195 / 226 (FP16 x 1000 34.3 / 36.0, x
+// 4096 107 / 133); 16384 x 100 19.8 / 41.2, x 1000 112 / 121, x 4096 407 / 578.
+// (One pass would win for some 700 to 2000 FP32 columns of 8192 points, which
+// this rule does not tell apart.)  A forced column shape (MI355FFT_COL_VARIANT)
+// keeps the single pass.
 bool column_split(int64_t n, int64_t stride, int64_t dist) {
     const char *cv = std::getenv("MI355FFT_COL_VARIANT");
     if (cv && cv[0]) return false;
