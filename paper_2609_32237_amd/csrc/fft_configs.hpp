@@ -158,7 +158,7 @@ struct Configs<4096> {
                        KCfg<4096, 32, 8, true, XCHG_SPLIT, 2, false, Radices<16, 16, 16>>,
                        // two radix-64 stages, 64 points per thread: one exchange per
                        // transform instead of two, and fewer VALU instructions per
-                       // point (100 against 106 for the matched pass)
+                       // point (87 against 93 for the matched pass)
                        KCfg<4096, 64, 8, true, XCHG_SPLIT, 1, false, Radices<64, 64>>,
                        KCfg<4096, 64, 4, true, XCHG_SPLIT, 1, false, Radices<64, 64>>>;
     // 8-column strips measured fastest for both column passes: 64-byte row

@@ -296,7 +296,7 @@ __device__ __forceinline__ void tw_apply(const TwRegs<K, NS, R> &tr, float2 (&u)
 // The stage's DFT with its twiddles.  LAYERED (FP16 data): with the digit-base
 // reads the layers need only the powers W^(k 2^i): the even ones are read, the
 // odd ones their squares (reading all of them was 2-6% slower: 16384 FP16 rows
-// 425-436 against 437-447 us).  Per point of a 16384-point FP16 row 45 VALU
+// 425-436 against 437-447 us).  Per point of a 16384-point FP16 row 46 VALU
 // instructions against 52 with the products.  FP32 data multiplies first: its
 // overflow and rounding are DftLayers' concern, and keeping both outputs of
 // the layers' butterflies as multiply-adds of the inputs, which has neither

@@ -473,8 +473,9 @@ int fft_plan_create_ex(int64_t n, int64_t batch, int64_t stride, int64_t dist, i
     // each row); three passes of at most 1024-point columns move the data
     // once more but faster: n1 = 2^floor(log2 n / 3) and n2 = n / n1 =
     // na * nb, na = 2^floor(log2 n2 / 2).  Measured on MI355X (1 GiB,
-    // 16 B/pt): 2^23 1.74 against 1.59 TB/s, 2^24 1.81 against 1.69,
-    // 2^28 1.25 against 0.47; at 2^20-2^22 two passes stay ahead.
+    // 16 B/pt; 8 columns of 4096 points at 32 points per thread, a shape the
+    // first pass no longer has): 2^23 1.74 against 1.59 TB/s, 2^24 1.81
+    // against 1.69, 2^28 1.25 against 0.47; at 2^20-2^22 two passes were ahead.
     const bool colsplit = !half_x && !mfma && column_split(n, stride, dist);
     const bool split = four_step || may_split || colsplit;
     const bool three = four_step && n > kMaxTwoPass;
@@ -725,9 +726,9 @@ size_t sar_workspace_bytes(int64_t n_az, int64_t n_rg, int inter_storage) {
 // points or more it runs instead as three passes of short columns in the
 // four-step form (n_az = n1 * n2, n1 = 128, j = n2 j1 + j2, k = k1 + n1 k2),
 // each reading and writing wide pieces of the rows.  Measured, three passes
-// against one: 16384 x 4096 859 / 898 us, x 8192 1775 / 1778, but x 2048 436 /
-// 414 and x 1024 218 / 202; 8192 pulses (four columns a workgroup) x 1024 117
-// / 94, x 2048 210 / 177, x 4096 435 / 388, x 8192 886 / 810.
+// against one: 16384 x 4096 856 / 903 us, x 8192 1733 / 1707, but x 2048 441 /
+// 412 and x 1024 215 / 200; 8192 pulses (four columns a workgroup) lost to one
+// pass everywhere, x 1024 117 / 94, x 8192 886 / 810.
 //   B1  for each j2: 128-point FFTs down rows n2 j1 + j2, output k1 times
 //       W^(j2 k1), to rows j2 n1 + k1 of the workspace;
 //   B2  in place, for each k1: n2-point FFT down rows j2 n1 + k1 (giving
