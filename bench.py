@@ -204,7 +204,7 @@ def _with_env(env, fn):
 
 def twiddle_experiment(torch, api, flush, samples):
     """The inter-stage twiddles formed by products of per-digit table reads
-    (the default) against every factor read from per-stage tables in lane
+    (FP16 data: squared powers in the butterflies' layers) against every factor read from per-stage tables in lane
     order, on the benchmark's FFT workloads and on the two SAR chains, each
     kernel shape forced by its index in the size's lists.  Flushed samples are
     interleaved across all cases after a clock warm-up."""
@@ -216,7 +216,7 @@ def twiddle_experiment(torch, api, flush, samples):
     for name, pairs in (("fft_n4096_b32768_fp32", ((0, "products"), (6, "stage tables"))),
                         ("fft_n8192_b16384_fp32", ((0, "products"), (6, "stage tables"))),
                         ("fft_n16384_b8192_fp32", ((4, "products"), (5, "stage tables"))),
-                        ("fft_n16384_b16384_fp16", ((4, "products"), (5, "stage tables")))):
+                        ("fft_n16384_b16384_fp16", ((4, "squared powers in the layers"), (5, "stage tables")))):
         w = workloads.FFT_WORKLOADS[name]
         n, batch, st = w["n"], w["batch"], 0 if w["storage"] == "fp32" else 1
         x = torch.from_numpy(workloads.fft_workload(name)).cuda()
